@@ -306,13 +306,18 @@ ipv_status ipv_ckv_step(const ipv_shape* shape, void* K, void* V, int32_t* frame
  * frames_V ([n_frames, B, L, H, rows, D], device, 16-byte aligned), frame id
  * first_frame_id + f and first_patch 0. n_tokens (host, [B]) holds the row
  * counts on entry and receives them on return; passes (host, [B]) receives how
- * many times each stream was compressed. The frames between two passes go
- * out as one append launch (the result is that of one append per frame).
+ * many times each stream was compressed. The passes run over the frames where
+ * they lie: between two passes of a stream only its metadata is compacted, and
+ * its surviving rows are written into K and V once, after its last pass of the
+ * call (the result is that of one append per frame and one compaction per
+ * pass); the frames after that are appended. frames_K / frames_V must not
+ * overlap K / V.
  * Every step is checked before the first is enqueued (the counts of the
  * whole stretch follow from the counts, rows, mem_cap and budget), so a
  * rejected call enqueues nothing. The only error that can come after the
- * first launch is IPV_ERR_HIP (the runtime refused a launch or a copy);
- * n_tokens and passes then describe the frames enqueued before it. The work
+ * first launch is IPV_ERR_HIP (the runtime refused a launch or a copy): the
+ * caches' contents are then unspecified and n_tokens holds the counts it came
+ * with. The work
  * of all frames shares tar, van, keep_idx and the workspace, which hold the
  * last pass's values on return. Problems only the device sees (IPV_DEV_* bits)
  * accumulate in the workspace's error word over all passes of the call and do

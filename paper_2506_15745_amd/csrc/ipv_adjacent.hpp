@@ -36,11 +36,12 @@ constexpr int kPrevMaxPositions = 8192;
 // The chunk's frame ids are double-buffered in LDS; a chunk costs six
 // barriers and no global-memory round trip (the next chunk's loads are in
 // flight meanwhile). One slice's walk is one block of kPrevThreads threads.
+template <class ST>
 __device__ __forceinline__ void prev_rows_block(int64_t slice, const int32_t* __restrict__ frame_idx,
                                                 const int32_t* __restrict__ patch_idx, int64_t S, int32_t n,
                                                 int32_t r, int32_t p, int32_t* __restrict__ prev,
                                                 int32_t* __restrict__ first_recent, uint32_t* err,
-                                                uint32_t* __restrict__ zero, int32_t zero_per_slice) {
+                                                uint32_t* __restrict__ zero, int32_t zero_per_slice, const ST& st) {
   constexpr int NT = kPrevThreads;
   constexpr int BPT = (kPrevMaxPositions + 1 + NT - 1) / NT;  // scan entries per thread
   __shared__ int32_t last[kPrevMaxPositions];
@@ -60,10 +61,12 @@ __device__ __forceinline__ void prev_rows_block(int64_t slice, const int32_t* __
     carry_frame = INT32_MIN;
     carry_start = 0;
   }
-  const int64_t thr = (int64_t)frame_idx[base + n - 1] - r + 1;
+  auto frame_at = [&](int64_t x) { return row_frame(st, x, frame_idx[base + x]); };
+  auto patch_at = [&](int64_t x) { return row_patch(st, x, patch_idx[base + x]); };
+  const int64_t thr = (int64_t)frame_at((int64_t)n - 1) - r + 1;
   uint32_t ebits = 0;
-  int32_t nf = frame_idx[base + min((int64_t)tid, (int64_t)n - 1)];
-  int32_t np = patch_idx[base + min((int64_t)tid, (int64_t)n - 1)];
+  int32_t nf = frame_at(min((int64_t)tid, (int64_t)n - 1));
+  int32_t np = patch_at(min((int64_t)tid, (int64_t)n - 1));
   int b = 0;
   for (int64_t c0 = 0; c0 < n; c0 += NT, b ^= 1) {
     const int64_t x = c0 + tid;
@@ -74,8 +77,8 @@ __device__ __forceinline__ void prev_rows_block(int64_t slice, const int32_t* __
     __syncthreads();  // (A) chunk metadata visible; counters zero
     {  // the next chunk's metadata is on its way meanwhile
       const int64_t xn = min(c0 + NT + tid, (int64_t)n - 1);
-      nf = frame_idx[base + xn];
-      np = patch_idx[base + xn];
+      nf = frame_at(xn);
+      np = patch_at(xn);
     }
     const int32_t rank = inq ? atomicAdd(&cnt[q], 1) : 0;
     __syncthreads();  // (B) counts complete
@@ -151,7 +154,7 @@ __global__ __launch_bounds__(kPrevThreads) void k_prev_rows(const int32_t* __res
                                                             int32_t* __restrict__ prev,
                                                             int32_t* __restrict__ first_recent, uint32_t* err,
                                                             uint32_t* __restrict__ zero, int32_t zero_per_slice) {
-  prev_rows_block(blockIdx.x, frame_idx, patch_idx, S, n, r, p, prev, first_recent, err, zero, zero_per_slice);
+  prev_rows_block(blockIdx.x, frame_idx, patch_idx, S, n, r, p, prev, first_recent, err, zero, zero_per_slice, Whole{});
 }
 
 // The prev-row walk and the VaN tiles of the sweep in one launch (VaN needs
@@ -167,7 +170,7 @@ __global__ __launch_bounds__(kPrevThreads) void k_prev_van(const T* __restrict__
     uint32_t prev_padded, uint32_t slices, float* __restrict__ van, TileGrid g) {
   if (blockIdx.x < prev_padded) {
     if (blockIdx.x < slices)
-      prev_rows_block(blockIdx.x, frame_idx, patch_idx, S, n, r, p, prev, first_recent, err, zero, zero_per_slice);
+      prev_rows_block(blockIdx.x, frame_idx, patch_idx, S, n, r, p, prev, first_recent, err, zero, zero_per_slice, Whole{});
     return;
   }
   using C = SweepCfg<T, D>;

@@ -13,6 +13,7 @@
 #include "ipv_compact.hpp"
 #include "ipv_scores.hpp"
 #include "ipv_select.hpp"
+#include "ipv_stretch.hpp"
 
 using namespace ipv;
 
@@ -261,14 +262,15 @@ ipv_status scores(const Dims& d, const void* K, const void* V, const int32_t* fr
 }
 
 // cv_done: the TaR launch has computed the windows already (k_tar_sweep_cv)
+template <class ST = Whole>
 ipv_status pool_d(const Dims& d, const double* tau, float* van, const int32_t* fr, const int32_t* pa, int32_t n,
-                  int32_t* pool_out, void* ws, hipStream_t st, bool cv_done = false) {
+                  int32_t* pool_out, void* ws, hipStream_t st, bool cv_done = false, const ST& rows = ST{}) {
   if (!cv_done)
     k_pool_cv<<<dim3((uint32_t)(d.B * d.L)), dim3(kPoolThreads), 0, st>>>(van, d.S, n, (int32_t)d.H, tau[0], tau[1],
                                                                           tau[2], ws_pool(ws, d), pool_out);
   k_pool_apply<<<dim3((uint32_t)d.slices), dim3(kPoolThreads), 0, st>>>(
       van, fr, pa, d.S, n, (int32_t)d.H, d.gh, d.gw, ws_pool(ws, d), make_fastdiv((uint32_t)d.p),
-      make_fastdiv((uint32_t)d.gw));
+      make_fastdiv((uint32_t)d.gw), rows);
   return launched();
 }
 
@@ -289,9 +291,10 @@ uint32_t sel_threads(int32_t n, int RPT) {
 
 // mode: the reverse bits complement a stage's keys; IPV_HEAD_SHARED gives one
 // block (and one keep set) to each (stream, layer)
-template <int RPT>
+template <int RPT, class ST, class EM>
 ipv_status run_select(const Dims& d, const float* tar, const float* van, const int32_t* fr, int32_t n, int32_t budget,
-                      int32_t tar_total, int32_t r, int32_t* keep, uint32_t* err, hipStream_t st, uint32_t mode) {
+                      int32_t tar_total, int32_t r, int32_t* keep, uint32_t* err, hipStream_t st, uint32_t mode,
+                      const ST& rows, const EM& em) {
   const int32_t heads = (mode & IPV_HEAD_SHARED) ? (int32_t)d.H : 1;
   const uint32_t tflip = (mode & IPV_TAR_REVERSE) ? 0xffffffffu : 0u;
   const uint32_t vflip = (mode & IPV_VAN_REVERSE) ? 0xffffffffu : 0u;
@@ -299,34 +302,37 @@ ipv_status run_select(const Dims& d, const float* tar, const float* van, const i
   // 16-byte row-run loads need every slice to start 16-byte aligned
   if (d.S % 4 == 0)
     k_select<kSelThreads, RPT, true><<<grid, block, 0, st>>>(tar, van, fr, d.S, n, budget, tar_total, r, keep, err,
-                                                             heads, tflip, vflip);
+                                                             heads, tflip, vflip, rows, em);
   else
     k_select<kSelThreads, RPT, false><<<grid, block, 0, st>>>(tar, van, fr, d.S, n, budget, tar_total, r, keep, err,
-                                                              heads, tflip, vflip);
+                                                              heads, tflip, vflip, rows, em);
   return launched();
 }
 
 // Uniform Select: one block per slice, or per (stream, layer) with
 // IPV_HEAD_SHARED. zero (may be null): the blocks also zero zero_per_slice
 // words per slice there (the compaction flags of the pass).
-template <int RPT>
+template <int RPT, class ST, class EM>
 ipv_status run_uniform(const Dims& d, const int32_t* fr, int32_t n, int32_t budget, int32_t r, int32_t* keep,
-                       uint32_t* err, hipStream_t st, uint32_t mode, uint32_t* zero, int32_t zero_per_slice) {
+                       uint32_t* err, hipStream_t st, uint32_t mode, uint32_t* zero, int32_t zero_per_slice,
+                       const ST& rows, const EM& em) {
   const int32_t heads = (mode & IPV_HEAD_SHARED) ? (int32_t)d.H : 1;
   const dim3 grid((uint32_t)(d.slices / heads)), block(sel_threads(n, RPT));
   if (d.S % 4 == 0)
     k_select_uniform<kSelThreads, RPT, true><<<grid, block, 0, st>>>(fr, d.S, n, budget, r, keep, err, heads, zero,
-                                                                     zero_per_slice);
+                                                                     zero_per_slice, rows, em);
   else
     k_select_uniform<kSelThreads, RPT, false><<<grid, block, 0, st>>>(fr, d.S, n, budget, r, keep, err, heads, zero,
-                                                                      zero_per_slice);
+                                                                      zero_per_slice, rows, em);
   return launched();
 }
 
-// zero / zero_per_slice: as for run_uniform (used by Uniform Select only)
+// zero / zero_per_slice: as for run_uniform (used by Uniform Select only).
+// rows / em: a Stretch and its Emit for a pass over rows outside the cache.
+template <class ST = Whole, class EM = NoEmit>
 ipv_status select(const Dims& d, const float* tar, const float* van, const int32_t* fr, int32_t n, int32_t budget,
                   int32_t tar_total, int32_t r, int32_t* keep, uint32_t* err, hipStream_t st, uint32_t mode,
-                  uint32_t* zero = nullptr, int32_t zero_per_slice = 0) {
+                  uint32_t* zero = nullptr, int32_t zero_per_slice = 0, const ST& rows = ST{}, const EM& em = EM{}) {
   const int32_t rpt = (n + kSelThreads - 1) / kSelThreads;
   // A block of up to 8 rows a thread (832 threads for 6272 rows) holds a CU
   // alone; with more blocks than CUs, 16 rows a thread (half the threads)
@@ -334,21 +340,25 @@ ipv_status select(const Dims& d, const float* tar, const float* van, const int32
   // longer (16-stream 7B-class batch: 65 against 93 us).
   const int64_t groups = d.slices / ((mode & IPV_HEAD_SHARED) ? d.H : 1);
   const bool many = groups > kComputeUnits && rpt <= 8;
+#define IPV_UNIFORM(RPT) return run_uniform<RPT>(d, fr, n, budget, r, keep, err, st, mode, zero, zero_per_slice, rows, em)
+#define IPV_SELECT(RPT) return run_select<RPT>(d, tar, van, fr, n, budget, tar_total, r, keep, err, st, mode, rows, em)
   if (mode & IPV_UNIFORM_SELECT) {
-    if (many) return run_uniform<16>(d, fr, n, budget, r, keep, err, st, mode, zero, zero_per_slice);
-    if (rpt <= 4) return run_uniform<4>(d, fr, n, budget, r, keep, err, st, mode, zero, zero_per_slice);
-    if (rpt <= 8) return run_uniform<8>(d, fr, n, budget, r, keep, err, st, mode, zero, zero_per_slice);
-    if (rpt <= 16) return run_uniform<16>(d, fr, n, budget, r, keep, err, st, mode, zero, zero_per_slice);
-    if (rpt <= 32) return run_uniform<32>(d, fr, n, budget, r, keep, err, st, mode, zero, zero_per_slice);
-    return run_uniform<64>(d, fr, n, budget, r, keep, err, st, mode, zero, zero_per_slice);
+    if (many) IPV_UNIFORM(16);
+    if (rpt <= 4) IPV_UNIFORM(4);
+    if (rpt <= 8) IPV_UNIFORM(8);
+    if (rpt <= 16) IPV_UNIFORM(16);
+    if (rpt <= 32) IPV_UNIFORM(32);
+    IPV_UNIFORM(64);
   }
-  if (many) return run_select<16>(d, tar, van, fr, n, budget, tar_total, r, keep, err, st, mode);
-  if (rpt <= 4) return run_select<4>(d, tar, van, fr, n, budget, tar_total, r, keep, err, st, mode);
-  if (rpt <= 8) return run_select<8>(d, tar, van, fr, n, budget, tar_total, r, keep, err, st, mode);
-  if (rpt <= 12) return run_select<12>(d, tar, van, fr, n, budget, tar_total, r, keep, err, st, mode);
-  if (rpt <= 16) return run_select<16>(d, tar, van, fr, n, budget, tar_total, r, keep, err, st, mode);
-  if (rpt <= 32) return run_select<32>(d, tar, van, fr, n, budget, tar_total, r, keep, err, st, mode);
-  return run_select<64>(d, tar, van, fr, n, budget, tar_total, r, keep, err, st, mode);
+  if (many) IPV_SELECT(16);
+  if (rpt <= 4) IPV_SELECT(4);
+  if (rpt <= 8) IPV_SELECT(8);
+  if (rpt <= 12) IPV_SELECT(12);
+  if (rpt <= 16) IPV_SELECT(16);
+  if (rpt <= 32) IPV_SELECT(32);
+  IPV_SELECT(64);
+#undef IPV_UNIFORM
+#undef IPV_SELECT
 }
 
 int64_t compact_chunks(int32_t budget) { return (budget + kCompactRows - 1) / kCompactRows; }
@@ -379,6 +389,94 @@ ipv_status compact(const Dims& d, void* K, void* V, int32_t* fr, int32_t* pa, in
     case 256: return run_compact<256>(d, K, V, fr, pa, n, keep, budget, ws, st, flags_zeroed);
     case 512: return run_compact<512>(d, K, V, fr, pa, n, keep, budget, ws, st, flags_zeroed);
     case 1024: return run_compact<1024>(d, K, V, fr, pa, n, keep, budget, ws, st, flags_zeroed);
+  }
+  return IPV_ERR_SHAPE;
+}
+
+// ------------------------------------------------------------ passes over a stretch (ipv_stretch.hpp)
+// Scores of one pass over a run of slices. norms_known: van holds the old
+// rows' norms already. cv_tau: the TaR launch also computes the pooling CV.
+// zero_chunks > 0: the first kernel zeroes the flags of a gather that follows.
+template <typename T, int D>
+ipv_status stretch_scores_t(const Dims& d, const char* K, const char* V, const Stretch& sr, const int32_t* fr,
+                            const int32_t* pa, int32_t n, int32_t r, float* tar, float* van, void* ws, hipStream_t st,
+                            int64_t zero_chunks, bool adjacent, const double* cv_tau, bool norms_known) {
+  using C = SweepCfg<T, D>;
+  constexpr uint32_t TILE = C::GROUPS * C::U;
+  uint32_t* zero = zero_chunks > 0 ? ws_flags(ws, d) : nullptr;
+  const int32_t zero_per_slice = (int32_t)(compact_parts(d) * walk_words(zero_chunks));
+  const uint32_t slices = (uint32_t)d.slices;
+  const uint32_t v0 = norms_known ? sr.n0 : 0u;
+  const uint32_t van_tiles = ((uint32_t)n - v0 + TILE - 1) / TILE, van_work = slices * van_tiles;
+  int32_t* first = ws_first(ws, d);
+  if (adjacent) {
+    const uint32_t walks = pad8(slices), quads = pad8((van_work + 3) / 4);
+    k_stretch_prev_van<T, D><<<dim3(walks + quads), dim3(kPrevThreads), 0, st>>>(
+        V, sr, fr, pa, d.S, n, r, (int32_t)d.p, ws_prev(ws), first, err_word(ws), zero, zero_per_slice, walks, slices,
+        van, v0, make_fastdiv(van_tiles), van_work, quads);
+    const uint32_t tiles = ((uint32_t)n + TILE - 1) / TILE, work = slices * tiles;
+    k_stretch_adjacent<T, D><<<dim3(pad8(work)), dim3(256), 0, st>>>(K, sr, ws_prev(ws), d.S, n, first, tar,
+                                                                     make_fastdiv(tiles), work, pad8(work));
+    return launched();
+  }
+  const uint32_t blocks = (uint32_t)((d.p + C::GROUPS - 1) / C::GROUPS), table = slices * blocks;
+  k_stretch_table_van<T, D><<<dim3(pad8(table) + pad8(van_work)), dim3(256), (size_t)C::GROUPS * r * sizeof(int32_t), st>>>(
+      K, V, sr, fr, pa, d.S, n, r, (int32_t)d.p, make_fastdiv(blocks), pad8(table), table, ws_table(ws), first,
+      err_word(ws), zero, zero_per_slice, van, v0, make_fastdiv(van_tiles), van_work, pad8(van_work));
+  const uint32_t rows = sr.rows.d, new_frames = ((uint32_t)n - sr.n0) / rows;
+  const uint32_t old_tiles = (sr.n0 + TILE - 1) / TILE, cols = (rows + C::GROUPS - 1) / C::GROUPS;
+  const uint32_t tiles = old_tiles + (new_frames + C::U - 1) / C::U * cols, work = slices * tiles;
+  const uint32_t cv = cv_tau ? (uint32_t)(d.B * d.L) : 0u;
+  const int32_t sure_past = (int32_t)std::max<int64_t>(0, (int64_t)n - (int64_t)r * d.p);
+  k_stretch_tar<T, D><<<dim3(pad8(cv) + pad8(work)), dim3(256), 0, st>>>(
+      K, sr, pa, d.S, n, (int32_t)d.p, ws_table(ws), first, tar, err_word(ws), make_fastdiv(tiles), old_tiles,
+      make_fastdiv(cols), work, pad8(work), sure_past, van, (int32_t)d.H, cv ? cv_tau[0] : 0.0, cv ? cv_tau[1] : 0.0,
+      cv ? cv_tau[2] : 0.0, ws_pool(ws, d), pad8(cv), cv);
+  return launched();
+}
+
+ipv_status stretch_scores(const Dims& d, const char* K, const char* V, const Stretch& sr, const int32_t* fr,
+                          const int32_t* pa, int32_t n, int32_t r, float* tar, float* van, void* ws, hipStream_t st,
+                          int64_t zero_chunks, bool adjacent, const double* cv_tau, bool norms_known) {
+#define IPV_SCORES(T, DD)                                                                                           \
+  if (d.D == DD)                                                                                                    \
+    return stretch_scores_t<T, DD>(d, K, V, sr, fr, pa, n, r, tar, van, ws, st, zero_chunks, adjacent, cv_tau, norms_known);
+  if (d.dtype == IPV_BF16) {
+    IPV_SCORES(uint16_t, 32) IPV_SCORES(uint16_t, 64) IPV_SCORES(uint16_t, 128) IPV_SCORES(uint16_t, 256)
+  } else {
+    IPV_SCORES(float, 32) IPV_SCORES(float, 64) IPV_SCORES(float, 128) IPV_SCORES(float, 256)
+  }
+#undef IPV_SCORES
+  return IPV_ERR_SHAPE;
+}
+
+// src: places of the budget rows that stay, [slices, S]; n_entry: rows the
+// cache held before the call
+template <int RB>
+ipv_status stretch_gather_t(const Dims& d, void* K, void* V, const Stretch& sr, const int32_t* src, int32_t n_entry,
+                            int32_t budget, void* ws, hipStream_t st) {
+  using C = CompactCfg<RB, kCompactThreads, kCompactRows, kCompactColBytes>;
+  const uint32_t chunks = (uint32_t)compact_chunks(budget), walks = (uint32_t)(d.slices * 2 * C::NCB);
+  const dim3 grid(walks * chunks), block(kCompactThreads);
+  if (n_entry > 0)
+    k_stretch_gather<RB, kCompactThreads, kCompactRows, kCompactColBytes, true><<<grid, block, 0, st>>>(
+        static_cast<char*>(K), static_cast<char*>(V), sr, src, d.S, n_entry, budget, err_word(ws), ws_flags(ws, d),
+        chunks, make_fastdiv(walks));
+  else
+    k_stretch_gather<RB, kCompactThreads, kCompactRows, kCompactColBytes, false><<<grid, block, 0, st>>>(
+        static_cast<char*>(K), static_cast<char*>(V), sr, src, d.S, n_entry, budget, err_word(ws), ws_flags(ws, d),
+        chunks, make_fastdiv(walks));
+  return launched();
+}
+
+ipv_status stretch_gather(const Dims& d, void* K, void* V, const Stretch& sr, const int32_t* src, int32_t n_entry,
+                          int32_t budget, void* ws, hipStream_t st) {
+  switch (d.D * d.elem) {
+    case 64: return stretch_gather_t<64>(d, K, V, sr, src, n_entry, budget, ws, st);
+    case 128: return stretch_gather_t<128>(d, K, V, sr, src, n_entry, budget, ws, st);
+    case 256: return stretch_gather_t<256>(d, K, V, sr, src, n_entry, budget, ws, st);
+    case 512: return stretch_gather_t<512>(d, K, V, sr, src, n_entry, budget, ws, st);
+    case 1024: return stretch_gather_t<1024>(d, K, V, sr, src, n_entry, budget, ws, st);
   }
   return IPV_ERR_SHAPE;
 }
@@ -522,26 +620,39 @@ int64_t kv_bytes_per_stream(const Dims& d) { return d.L * d.H * d.S * d.D * d.el
 int64_t rows_per_stream(const Dims& d) { return d.L * d.H * d.S; }
 
 // Frames [0, frames) of K_new / V_new (frame j at byte j * frame_stride; in
-// a frame the batch's [B, L, H, rows, D] layout) appended to every stream
-// after its n_tokens[b] rows; one launch per run of equal counts (an empty
-// stream appends at row 0 like any other). Arguments checked by the caller.
-ipv_status append_frames(const Dims& d, void* K, void* V, int32_t* frame_idx, int32_t* patch_idx,
-                         const int32_t* n_tokens, const void* K_new, const void* V_new, int32_t rows, int32_t frames,
-                         int64_t frame_stride, int32_t frame_id, int32_t first_patch, hipStream_t st) {
+// a frame the batch's [B, L, H, rows, D] layout) appended after row n of every
+// slice of streams [b, e). Arguments checked by the caller.
+ipv_status append_run(const Dims& d, int64_t b, int64_t e, void* K, void* V, int32_t* frame_idx, int32_t* patch_idx,
+                      int32_t n, const void* K_new, const void* V_new, int32_t rows, int32_t frames,
+                      int64_t frame_stride, int32_t frame_id, int32_t first_patch, hipStream_t st) {
   const int64_t RB = d.D * d.elem;
   const int64_t kb = kv_bytes_per_stream(d), rs = rows_per_stream(d), nb = d.L * d.H * (int64_t)rows * RB;
-  const int64_t pieces = (int64_t)frames * rows * (RB / 16);
-  for (int64_t b = 0; b < d.B;) {
-    const int32_t n = n_tokens[b];
-    int64_t e = b + 1;
-    while (e < d.B && n_tokens[e] == n) ++e;
-    const int64_t slices = (e - b) * d.L * d.H;
-    const dim3 grid((uint32_t)std::min<int64_t>((pieces + 255) / 256, 256), (uint32_t)std::min<int64_t>(slices, 65535));
-    k_append<<<grid, dim3(256), 0, st>>>(static_cast<const char*>(K_new) + b * nb,
-                                         static_cast<const char*>(V_new) + b * nb, static_cast<char*>(K) + b * kb,
-                                         static_cast<char*>(V) + b * kb, frame_idx + b * rs, patch_idx + b * rs, d.S, n,
-                                         rows, frames, frame_stride, RB, frame_id, first_patch, slices);
-    IPV_TRY(launched());
+  const int64_t pieces = (int64_t)frames * rows * (RB / 16), slices = (e - b) * d.L * d.H;
+  const dim3 grid((uint32_t)std::min<int64_t>((pieces + 255) / 256, 256), (uint32_t)std::min<int64_t>(slices, 65535));
+  k_append<<<grid, dim3(256), 0, st>>>(static_cast<const char*>(K_new) + b * nb,
+                                       static_cast<const char*>(V_new) + b * nb, static_cast<char*>(K) + b * kb,
+                                       static_cast<char*>(V) + b * kb, frame_idx + b * rs, patch_idx + b * rs, d.S, n,
+                                       rows, frames, frame_stride, RB, frame_id, first_patch, slices);
+  return launched();
+}
+
+// A stream's place in a call of the continual-compression loop.
+struct LoopStream {
+  int32_t n0;       // rows before its pending frames
+  int32_t pending;  // first frame of the call that is not in a pass yet
+  int32_t passes, total;  // passes so far and in the whole call
+  bool operator==(const LoopStream& o) const {
+    return n0 == o.n0 && pending == o.pending && passes == o.passes && total == o.total;
+  }
+};
+
+// fn(b, e) for every maximal run [b, e) of streams that are alike and satisfy want
+template <typename W, typename F>
+ipv_status for_alike(const std::vector<LoopStream>& ls, W want, F fn) {
+  for (size_t b = 0; b < ls.size();) {
+    size_t e = b + 1;
+    while (e < ls.size() && ls[e] == ls[b]) ++e;
+    if (want(ls[b])) IPV_TRY(fn((int64_t)b, (int64_t)e));
     b = e;
   }
   return IPV_OK;
@@ -693,6 +804,100 @@ ipv_status scratch_of(hipStream_t st, void** out) {
   return IPV_OK;
 }
 
+// Frames [0, n_frames) of a call of the continual-compression loop whose
+// arguments are checked: the passes run over the frames where they lie, one
+// gather per stream follows its last pass, and the frames after that are
+// appended. The places of a stream's rows between two passes are kept in its
+// rows of keep_idx, its value norms in van (without pooling, which overwrites
+// them); the last pass leaves its keep set and scores there, and the places of
+// the rows that stay in the workspace's table region, whose contents (the m
+// vectors or prev rows) the pass has used by then.
+ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int32_t* patch_idx, int32_t* n_tokens,
+                       const char* fk, const char* fv, int32_t n_frames, int32_t rows, int32_t first_frame_id,
+                       int32_t mem_cap, int32_t budget, double alpha, int32_t r, uint32_t mode, const double* cv_tau,
+                       float* tar, float* van, int32_t* keep_idx, void* ws, int32_t* passes, hipStream_t st) {
+  const int64_t kb = kv_bytes_per_stream(d), rs = rows_per_stream(d), ks = d.L * d.H * (int64_t)budget;
+  const int64_t nb = d.L * d.H * (int64_t)rows * d.D * d.elem, frame_bytes = d.B * nb;
+  const bool uniform = (mode & IPV_UNIFORM_SELECT) != 0, adjacent = (mode & IPV_TAR_ADJACENT) != 0;
+  const bool pool = cv_tau && !uniform;
+  auto fires_in = [&](int32_t n) { return (mem_cap - n + rows - 1) / rows; };  // frames until the cap, the last included
+  std::vector<LoopStream> ls((size_t)d.B);
+  for (int64_t b = 0; b < d.B; ++b) {
+    ls[b] = {n_tokens[b], 0, 0, 0};
+    // a budget equal to the cap fires once: the checks let no frame follow that pass
+    const int64_t later = fires_in(budget);
+    for (int64_t f = fires_in(n_tokens[b]); f <= n_frames; f += later) {
+      ++ls[b].total;
+      if (later < 1) break;
+    }
+  }
+  const std::vector<LoopStream> entry = ls;
+  for (;;) {
+    // the next frame at which a stream reaches the cap (frames [pending, f] are its new rows)
+    int64_t f = INT64_MAX;
+    for (const LoopStream& s : ls)
+      if (s.passes < s.total) f = std::min<int64_t>(f, (int64_t)s.pending + fires_in(s.n0) - 1);
+    if (f == INT64_MAX) break;
+    auto fires = [&](const LoopStream& s) { return s.passes < s.total && (int64_t)s.pending + fires_in(s.n0) - 1 == f; };
+    IPV_TRY(for_alike(ls, fires, [&](int64_t b0, int64_t b1) -> ipv_status {
+      for (int64_t e; b0 < b1; b0 = e) {  // streams that entered the call alike, too
+        for (e = b0 + 1; e < b1 && entry[e].n0 == entry[b0].n0;) ++e;
+        const Dims s = sub_batch(d, e - b0);
+        const LoopStream l = ls[b0];
+        const bool last = l.passes + 1 == l.total;
+        const int32_t n = l.n0 + (int32_t)(f + 1 - l.pending) * rows;
+        const int64_t chunks = last ? compact_chunks(budget) : 0;
+        char* k = static_cast<char*>(K) + b0 * kb;
+        char* v = static_cast<char*>(V) + b0 * kb;
+        int32_t* fr = frame_idx + b0 * rs;
+        int32_t* pa = patch_idx + b0 * rs;
+        int32_t* keep = keep_idx + b0 * ks;
+        float* tr = at_stream(tar, b0, rs);
+        float* vn = at_stream(van, b0, rs);
+        Stretch sr{};
+        sr.K = fk + b0 * nb;
+        sr.V = fv + b0 * nb;
+        sr.stride = frame_bytes;
+        sr.src = l.passes ? keep : nullptr;
+        sr.src_stride = budget;
+        sr.rows = make_fastdiv((uint32_t)rows);
+        sr.n0 = (uint32_t)l.n0;
+        sr.f0 = (uint32_t)l.pending;
+        sr.eoff = (uint32_t)l.pending * (uint32_t)rows - (uint32_t)l.n0;
+        sr.id0 = first_frame_id;
+        int32_t* places = reinterpret_cast<int32_t*>(ws_table(ws));
+        if (!uniform)
+          IPV_TRY(stretch_scores(s, k, v, sr, fr, pa, n, r, tr, vn, ws, st, chunks, adjacent,
+                                 pool && !adjacent ? cv_tau : nullptr, l.passes > 0 && !pool));
+        if (pool) IPV_TRY(pool_d(s, cv_tau, vn, fr, pa, n, nullptr, ws, st, !adjacent, sr));
+        const Emit em{fr,
+                      pa,
+                      last ? places : keep,
+                      last ? s.S : budget,
+                      last || pool || uniform ? nullptr : vn,
+                      last ? keep : nullptr};
+        IPV_TRY(select(s, tr, vn, fr, n, budget, floor_share(alpha, budget), r, keep, err_word(ws), st, mode,
+                       uniform && last ? ws_flags(ws, s) : nullptr, (int32_t)(compact_parts(s) * walk_words(chunks)), sr,
+                       em));
+        if (last) IPV_TRY(stretch_gather(s, k, v, sr, places, entry[b0].n0, budget, ws, st));
+        for (int64_t b = b0; b < e; ++b) {
+          ls[b] = {budget, (int32_t)f + 1, l.passes + 1, l.total};
+          ++passes[b];
+        }
+      }
+      return IPV_OK;
+    }));
+  }
+  // the frames after a stream's last pass
+  IPV_TRY(for_alike(ls, [&](const LoopStream& s) { return s.pending < n_frames; }, [&](int64_t b, int64_t e) {
+    const LoopStream l = ls[b];
+    return append_run(d, b, e, K, V, frame_idx, patch_idx, l.n0, fk + l.pending * frame_bytes, fv + l.pending * frame_bytes,
+                      rows, n_frames - l.pending, frame_bytes, first_frame_id + l.pending, 0, st);
+  }));
+  for (int64_t b = 0; b < d.B; ++b) n_tokens[b] = ls[b].n0 + (n_frames - ls[b].pending) * rows;
+  return IPV_OK;
+}
+
 __global__ void k_copy_word(uint32_t* dst, const uint32_t* src) {
   if (threadIdx.x == 0) *dst = *src;
 }
@@ -763,8 +968,13 @@ ipv_status ipv_append(const ipv_shape* shape, void* K, void* V, int32_t* frame_i
   for (int64_t b = 0; b < d.B; ++b)
     if (n_tokens[b] < 0 || (int64_t)n_tokens[b] + rows > d.S) return IPV_ERR_SHAPE;
   if (first_patch < 0 || (int64_t)first_patch + rows > d.p) return IPV_ERR_ARG;
-  return append_frames(d, K, V, frame_idx, patch_idx, n_tokens, K_new, V_new, rows, 1, 0, frame_id, first_patch,
-                       static_cast<hipStream_t>(stream));
+  // one launch per run of equal counts (an empty stream appends at row 0 like any other)
+  for (int64_t b = 0, e; b < d.B; b = e) {
+    for (e = b + 1; e < d.B && n_tokens[e] == n_tokens[b];) ++e;
+    IPV_TRY(append_run(d, b, e, K, V, frame_idx, patch_idx, n_tokens[b], K_new, V_new, rows, 1, 0, frame_id,
+                       first_patch, static_cast<hipStream_t>(stream)));
+  }
+  return IPV_OK;
 }
 
 ipv_status ipv_ckv_step(const ipv_shape* shape, void* K, void* V, int32_t* frame_idx, int32_t* patch_idx,
@@ -840,32 +1050,16 @@ ipv_status ipv_ckv_stream(const ipv_shape* shape, void* K, void* V, int32_t* fra
     if (!aligned(tar, 16) || !aligned(van, 16) || !aligned(keep_idx, 16)) return IPV_ERR_ALIGN;
     IPV_TRY(check_ws(d, ws, ws_bytes));
   }
-  const int64_t frame_bytes = d.slices * rows * d.D * d.elem;
-  const char* fk = static_cast<const char*>(frames_K);
-  const char* fv = static_cast<const char*>(frames_V);
   for (int64_t b = 0; b < d.B; ++b) passes[b] = 0;
-  std::vector<int32_t> n_out((size_t)d.B), fired((size_t)d.B);
-  for (int32_t f = 0; f < n_frames;) {
-    // frames [f, g) bring no stream to the cap: one append launch (per run of
-    // equal counts) for all of them; frame g is a step with its pass
-    int64_t until = INT64_MAX;  // frames until the first stream reaches the cap, that frame included
-    for (int64_t b = 0; b < d.B; ++b) until = std::min<int64_t>(until, (mem_cap - n_tokens[b] + rows - 1) / rows);
-    const int32_t g = (int32_t)std::min<int64_t>(n_frames, f + until - 1);
-    if (g > f) {
-      IPV_TRY(append_frames(d, K, V, frame_idx, patch_idx, n_tokens, fk + f * frame_bytes, fv + f * frame_bytes, rows,
-                            g - f, frame_bytes, first_frame_id + f, 0, static_cast<hipStream_t>(stream)));
-      for (int64_t b = 0; b < d.B; ++b) n_tokens[b] += (g - f) * rows;
-    }
-    if (g < n_frames) {
-      IPV_TRY(ipv_ckv_step(shape, K, V, frame_idx, patch_idx, n_tokens, fk + g * frame_bytes, fv + g * frame_bytes, rows,
-                           first_frame_id + g, 0, mem_cap, budget, alpha, recent_frames, mode, cv_tau, tar, van,
-                           keep_idx, ws, ws_bytes, n_out.data(), fired.data(), stream));
-      for (int64_t b = 0; b < d.B; ++b) {
-        n_tokens[b] = n_out[b];
-        passes[b] += fired[b];
-      }
-    }
-    f = g + 1;
+  // places of frame rows are 31-bit: longer calls are taken in parts
+  const int32_t part = std::max<int32_t>(1, (INT32_MAX - 1) / rows);
+  const int64_t frame_bytes = d.slices * rows * d.D * d.elem;
+  for (int32_t f = 0; f < n_frames; f += std::min(part, n_frames - f)) {
+    const int32_t count = std::min(part, n_frames - f);
+    IPV_TRY(stream_part(d, K, V, frame_idx, patch_idx, n_tokens, static_cast<const char*>(frames_K) + f * frame_bytes,
+                        static_cast<const char*>(frames_V) + f * frame_bytes, count, rows, first_frame_id + f, mem_cap,
+                        budget, alpha, recent_frames, mode, cv_tau, tar, van, keep_idx, ws, passes,
+                        static_cast<hipStream_t>(stream)));
   }
   return IPV_OK;
 }

@@ -275,6 +275,45 @@ __device__ __forceinline__ uint32_t fast_div(uint32_t x, const FastDiv& f) {
   return (t + ((x - t) >> f.s1)) >> f.s2;
 }
 
+// Where the rows of a launch's slices are. Whole: every row is in the cache.
+struct Whole {
+  static constexpr bool kNew = false;
+};
+
+// Rows [0, n0) of a slice are old rows, rows [n0, n) the pending frames of a
+// stretch of resident frames (`rows` rows each, frame f0 of the call the first
+// pending one), which are not in the cache yet (ipv_stretch.hpp). Frame
+// f of the call has frame id id0 + f and patch ids patch0, patch0 + 1, ...
+struct Stretch {
+  static constexpr bool kNew = true;
+  const char* K;      // the call's frames, at the launch's first slice: frame f of slice s
+  const char* V;      //   is `rows` contiguous rows at f * stride + s * rows * row bytes
+  int64_t stride;
+  const int32_t* src; // place of old row x of slice s: src[s * src_stride + x]; null: cache row x
+  int64_t src_stride;
+  FastDiv rows;
+  uint32_t n0, f0;
+  uint32_t eoff;      // f0 * rows - n0: new row x is row x + eoff of the call's frames
+  int32_t id0, patch0;
+  __device__ int32_t frame_of(uint32_t x) const { return id0 + (int32_t)fast_div(x + eoff, rows); }
+  __device__ int32_t patch_of(uint32_t x) const {
+    const uint32_t e = x + eoff;
+    return patch0 + (int32_t)(e - fast_div(e, rows) * rows.d);
+  }
+};
+
+// Row x's frame / patch id, given what the metadata array holds there.
+template <class ST>
+__device__ __forceinline__ int32_t row_frame(const ST& st, int64_t x, int32_t stored) {
+  if constexpr (ST::kNew) return x >= st.n0 ? st.frame_of((uint32_t)x) : stored;
+  return stored;
+}
+template <class ST>
+__device__ __forceinline__ int32_t row_patch(const ST& st, int64_t x, int32_t stored) {
+  if constexpr (ST::kNew) return x >= st.n0 ? st.patch_of((uint32_t)x) : stored;
+  return stored;
+}
+
 // Workgroups are dispatched round-robin over the 8 XCDs (id % 8). Renumber
 // them so that consecutive logical ids share an XCD and its L2: logical =
 // (id % 8) * per_xcd + id / 8. The grid must be padded to a multiple of 8;

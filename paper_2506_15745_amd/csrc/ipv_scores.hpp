@@ -135,7 +135,7 @@ __device__ __forceinline__ void table_block(const T* __restrict__ K, const int32
         const float ss = group_sum<LPR>(Lane<T>::sumsq(raw[b]));
         const float inv = ss > 0.f ? fast_rsqrt(ss) : 0.f;
 #pragma unroll
-        for (int i = 0; i < EPL; ++i) acc[i] += f[i] * inv;
+        for (int i = 0; i < EPL; ++i) acc[i] = __builtin_fmaf(f[i], inv, acc[i]);
       }
     }
     const float scale = cnt ? 1.f / (float)cnt : 0.f;
@@ -215,6 +215,30 @@ struct TileGrid {
   uint32_t n_work;
   uint32_t blocks;  // tile blocks of the launch (a multiple of 8), the XCD renumbering's grid
 };
+
+// The dot product and the sum of squares of one 16-byte chunk of a key row
+// against its m chunk. The fused multiply-adds are written out, so that every
+// kernel that scores a row gives it the same bits.
+template <typename T>
+__device__ __forceinline__ void tar_parts(const Raw16& k, const float4 (&m)[Lane<T>::EPL / 4], float (&part)[2]) {
+  constexpr int EPL = Lane<T>::EPL;
+  float f[EPL], dot = 0.f;
+  Lane<T>::decode(k, f);
+#pragma unroll
+  for (int i = 0; i < EPL; i += 4) {
+    const float4 mv = m[i / 4];
+    dot += __builtin_fmaf(f[i + 3], mv.w, __builtin_fmaf(f[i + 2], mv.z, __builtin_fmaf(f[i + 1], mv.y, f[i] * mv.x)));
+  }
+  part[0] = dot;
+  part[1] = Lane<T>::sumsq(k);
+}
+
+// A row's TaR score from its totals.
+__device__ __forceinline__ float tar_score(const float (&tot)[2]) {
+  float sc = tot[1] != 0.f ? -(tot[0] * fast_rsqrt(tot[1])) : 0.f;  // a NaN key gives NaN, as in exact arithmetic
+  if (sc == 0.f) sc = 0.f;                                          // -0.0 -> +0.0
+  return sc;
+}
 
 // One tile: 256 threads (tid in [0, 256)), columns [colblock * GROUPS, +GROUPS),
 // frames [f0, f0 + U). rec = the slice's first recent row. Row indices are
@@ -323,25 +347,12 @@ __device__ __forceinline__ void sweep_tile(const T* __restrict__ K, const T* __r
 #pragma unroll
         for (int i = 0; i < EPL / 4; ++i) m[i] = *reinterpret_cast<const float4*>(mq + 4 * i);
       }
-      float dot = 0.f, kk = 0.f;
-      if (ok) {
-        float f[EPL];
-        Lane<T>::decode(kr[u], f);
-#pragma unroll
-        for (int i = 0; i < EPL; i += 4) {
-          const float4 mv = m[i / 4];
-          dot += f[i] * mv.x + f[i + 1] * mv.y + f[i + 2] * mv.z + f[i + 3] * mv.w;
-        }
-        kk = Lane<T>::sumsq(kr[u]);
-      }
-      part[u][0] = dot;
-      part[u][1] = kk;
+      part[u][0] = part[u][1] = 0.f;
+      if (ok) tar_parts<T>(kr[u], m, part[u]);
     }
     float tot[2];
     reduce_scatter4<LPR, 2>(part, tot, lane);
-    float sc = tot[1] != 0.f ? -(tot[0] * fast_rsqrt(tot[1])) : 0.f;  // a NaN key gives NaN, as in exact arithmetic
-    if (sc == 0.f) sc = 0.f;  // -0.0 -> +0.0
-    if (storer) tar[base + x_mine] = x_mine < past_end ? sc : 0.f;
+    if (storer) tar[base + x_mine] = x_mine < past_end ? tar_score(tot) : 0.f;
   }
 }
 
@@ -550,12 +561,13 @@ __device__ __forceinline__ float window_col(const float* hsum, const uint8_t* hc
 // rows are loaded again in each pass.
 constexpr int kPoolCells = 8192;
 
+template <class ST>
 __global__ __launch_bounds__(kPoolThreads) void k_pool_apply(float* __restrict__ van,
                                                              const int32_t* __restrict__ frame_idx,
                                                              const int32_t* __restrict__ patch_idx, int64_t S,
                                                              int32_t n, int32_t H, int32_t grid_h, int32_t grid_w,
                                                              const int32_t* __restrict__ pool_ws, FastDiv pdiv,
-                                                             FastDiv wdiv) {
+                                                             FastDiv wdiv, ST st) {
   constexpr int NT = kPoolThreads, U = kPoolBatch, NW = NT / kWave;
   __shared__ float cell[kPoolCells];
   __shared__ float hsum[kPoolCells];
@@ -578,8 +590,8 @@ __global__ __launch_bounds__(kPoolThreads) void k_pool_apply(float* __restrict__
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const uint32_t off = (uint32_t)(tid + u * NT) * 4u;
-    f0[u] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(frs, off, 0, 0);
-    q0[u] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(prs, off, 0, 0);
+    f0[u] = row_frame(st, tid + u * NT, (int32_t)__builtin_amdgcn_raw_buffer_load_b32(frs, off, 0, 0));
+    q0[u] = row_patch(st, tid + u * NT, (int32_t)__builtin_amdgcn_raw_buffer_load_b32(prs, off, 0, 0));
     v0[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(vrs, off, 0, 0));
   }
   // rows x0 + u * NT of batch b (b == 0: the registers above); rows past n read as 0
@@ -596,8 +608,8 @@ __global__ __launch_bounds__(kPoolThreads) void k_pool_apply(float* __restrict__
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint32_t off = (uint32_t)(x0 + u * NT) * 4u;
-      f[u] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(frs, off, 0, 0);
-      q[u] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(prs, off, 0, 0);
+      f[u] = row_frame(st, x0 + u * NT, (int32_t)__builtin_amdgcn_raw_buffer_load_b32(frs, off, 0, 0));
+      q[u] = row_patch(st, x0 + u * NT, (int32_t)__builtin_amdgcn_raw_buffer_load_b32(prs, off, 0, 0));
       v[u] = need_v ? __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(vrs, off, 0, 0)) : 0.f;
     }
   };

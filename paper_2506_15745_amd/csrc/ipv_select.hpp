@@ -273,13 +273,13 @@ __device__ __forceinline__ bool heads_differ(const int32_t* __restrict__ fr0, in
 }
 
 // Writes the keep set: `kept` marks this thread's kept rows among its RPT
-// rows from row0, `pos` is the number of kept rows before them. `put(j, row)`
-// stores output position j. The set is gathered in LDS in output order,
-// kStageRows positions at a time, so that the global stores are consecutive
-// across the block.
-template <int NT, int RPT, typename Put>
+// rows from row0, `pos` is the number of kept rows before them. The set is
+// gathered in LDS in output order, kStageRows positions at a time;
+// `out(lo, hi)` stores positions [lo, hi) from sh.stage with consecutive
+// stores across the block.
+template <int NT, int RPT, typename Out>
 __device__ __forceinline__ void write_keep(uint64_t kept, int32_t pos, int32_t budget, int64_t row0,
-                                           SelShared<NT>& sh, Put put) {
+                                           SelShared<NT>& sh, Out out) {
   for (int32_t lo = 0; lo < budget; lo += kStageRows) {
     const int32_t hi = min(budget, lo + kStageRows);
     int32_t q = pos;
@@ -290,32 +290,113 @@ __device__ __forceinline__ void write_keep(uint64_t kept, int32_t pos, int32_t b
         ++q;
       }
     __syncthreads();
-    for (int32_t j = threadIdx.x; j < hi - lo; j += (int32_t)blockDim.x) put(lo + j, sh.stage[j]);
+    out(lo, hi);
     if (hi < budget) __syncthreads();  // the next positions reuse the stage
+  }
+}
+
+// The keep set 0..budget-1, through the same stage.
+template <int NT, typename Out>
+__device__ __forceinline__ void keep_first_rows(int32_t budget, SelShared<NT>& sh, Out out) {
+  for (int32_t lo = 0; lo < budget; lo += kStageRows) {
+    const int32_t hi = min(budget, lo + kStageRows);
+    for (int32_t j = lo + (int32_t)threadIdx.x; j < hi; j += (int32_t)blockDim.x) sh.stage[j - lo] = j;
+    __syncthreads();
+    out(lo, hi);
+    if (hi < budget) __syncthreads();
+  }
+}
+
+// Rows whose metadata is stored.
+template <class ST>
+__device__ __forceinline__ int32_t stored_rows(const ST& st, int32_t n) {
+  if constexpr (ST::kNew) return min(n, (int32_t)st.n0);
+  return n;
+}
+
+// What the selection of a pass over a stretch (ipv_stretch.hpp) compacts beside
+// writing the keep set: row j of the metadata, the place index and the value
+// norms <- row keep[j], in place, so a pass needs no compaction launch.
+struct Emit {
+  int32_t *frame_idx, *patch_idx;
+  int32_t* src;        // the new place index ([slices, src_stride]); may be where the old one is
+  int64_t src_stride;
+  float* norm;         // null: the norms are not needed again
+  int32_t* keep;       // [slices, budget]; null: this keep set is not the call's last
+};
+struct NoEmit {};
+
+// Output positions [lo, hi), whose rows stand in stage[0, hi - lo): every row
+// is at or after its position, so taking the positions in ascending batches
+// (all of a batch loaded before any of it is stored) never overwrites a row
+// that is still to be read. Every thread calls this.
+template <int NT>
+__device__ __forceinline__ void emit_rows(const Stretch& st, const Emit& em, int64_t S, int32_t n, int32_t budget,
+                                          int64_t slice, int32_t heads, int32_t lo, int32_t hi, const int32_t* stage) {
+  constexpr int U = 4;
+  const int bd = (int)blockDim.x;
+  for (int32_t h = 0; h < heads; ++h) {
+    const int64_t sl = slice + h;
+    int32_t* fr = em.frame_idx + sl * S;
+    int32_t* pa = em.patch_idx + sl * S;
+    float* nm = em.norm ? em.norm + sl * S : nullptr;
+    const int32_t* in = st.src ? st.src + sl * st.src_stride : nullptr;
+    int32_t* out = em.src + sl * em.src_stride;
+    int32_t* keep = em.keep ? em.keep + sl * budget : nullptr;
+    for (int32_t j0 = lo; j0 < hi; j0 += U * bd) {
+      int32_t row[U], f[U], q[U], s[U];
+      float v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int32_t j = j0 + u * bd + (int32_t)threadIdx.x;
+        row[u] = (int32_t)min((uint32_t)stage[min(j, hi - 1) - lo], (uint32_t)n - 1u);
+        const int32_t at = row[u] < (int32_t)st.n0 ? row[u] : 0;  // new rows: the ids are arithmetic
+        f[u] = row_frame(st, row[u], fr[at]);
+        q[u] = row_patch(st, row[u], pa[at]);
+        s[u] = row[u] < (int32_t)st.n0 ? (in ? in[at] : at) : ~(int32_t)(st.eoff + (uint32_t)row[u]);
+        v[u] = nm ? nm[row[u]] : 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) asm volatile("" ::"v"(f[u]), "v"(q[u]), "v"(s[u]), "v"(v[u]));
+      __syncthreads();  // every wave's loads of this batch have landed
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int32_t j = j0 + u * bd + (int32_t)threadIdx.x;
+        if (j < hi) {
+          fr[j] = f[u];
+          pa[j] = q[u];
+          out[j] = s[u];
+          if (nm) nm[j] = v[u];
+          if (keep) keep[j] = row[u];
+        }
+      }
+    }
   }
 }
 
 // One group of `heads` slices (1: a slice of its own) with NT threads. VEC:
 // every slice's row 0 is 16-byte aligned (capacity % 4 == 0) so row runs
 // load 16 bytes at a time. tflip / vflip: 0, or ~0 for a reversed stage.
-template <int NT, int RPT, bool VEC>
+// With a Stretch, the keep set goes through emit_rows.
+template <int NT, int RPT, bool VEC, class ST, class EM>
 __device__ __forceinline__ void select_slice(const float* __restrict__ tar, const float* __restrict__ van,
                              const int32_t* __restrict__ frame_idx, int64_t S, int32_t n, int32_t budget,
                              int32_t tar_total, int32_t r, int32_t* __restrict__ keep_idx,
                              uint32_t* err, int64_t slice, int32_t heads, uint32_t tflip, uint32_t vflip,
-                             SelShared<NT>& sh) {
+                             SelShared<NT>& sh, const ST& st, const EM& em) {
   constexpr int NW = NT / kWave;
   const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
   const int64_t base = slice * S;
   const int64_t row0 = (int64_t)tid * RPT;
-  int32_t* keep = keep_idx + slice * budget;
-  // every head of the group gets the same keep set
-  auto put = [&](int32_t j, int32_t row) {
-    if (heads == 1) {
-      keep[j] = row;
-      return;
+  // positions [lo, hi) of the keep set; every head of the group gets the same
+  auto out = [&](int32_t lo, int32_t hi) {
+    if constexpr (ST::kNew) {
+      emit_rows<NT>(st, em, S, n, budget, slice, heads, lo, hi, sh.stage);
+    } else {
+      int32_t* keep = keep_idx + slice * budget;
+      for (int32_t j = threadIdx.x; j < hi - lo; j += (int32_t)blockDim.x)
+        for (int32_t h = 0; h < heads; ++h) keep[(int64_t)h * budget + lo + j] = sh.stage[j];
     }
-    for (int32_t h = 0; h < heads; ++h) keep[(int64_t)h * budget + j] = row;
   };
 
   // all loads are issued up front; with many rows per thread the VaN column
@@ -326,9 +407,9 @@ __device__ __forceinline__ void select_slice(const float* __restrict__ tar, cons
   load_score_run<RPT, VEC>(tar + base, S, heads, row0, kt);
   if (kEarlyVan) load_score_run<RPT, VEC>(van + base, S, heads, row0, kv);
   const __amdgpu_buffer_rsrc_t frs = buffer_rsrc(frame_idx + base, (uint32_t)(S * 4));
-  const int32_t last = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(frs, (uint32_t)(n - 1) * 4u, 0, 0);
-  const int32_t prev_row = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(frs, (uint32_t)max(row0 - 1, (int64_t)0) * 4u,
-                                                                          0, 0);
+  const int32_t last = row_frame(st, n - 1, (int32_t)__builtin_amdgcn_raw_buffer_load_b32(frs, (uint32_t)(n - 1) * 4u, 0, 0));
+  const int32_t prev_row = row_frame(st, row0 - 1, (int32_t)__builtin_amdgcn_raw_buffer_load_b32(
+                                                       frs, (uint32_t)max(row0 - 1, (int64_t)0) * 4u, 0, 0));
   const int32_t before = row0 > 0 ? prev_row : INT32_MIN;
   for (int i = tid; i < kHistWords; i += (int)blockDim.x) sh.hist[0][i] = 0u;
   neutral_missing_waves<NT>(sh);
@@ -336,7 +417,11 @@ __device__ __forceinline__ void select_slice(const float* __restrict__ tar, cons
   const int64_t thr = (int64_t)last - r + 1;
   uint64_t valid = 0, recent = 0;
   int32_t prev = before;
-  bool bad = heads > 1 && heads_differ<RPT, VEC>(frame_idx + base, S, heads, row0, n, fr);
+  bool bad = heads > 1 && heads_differ<RPT, VEC>(frame_idx + base, S, heads, row0, stored_rows(st, n), fr);
+  if constexpr (ST::kNew) {
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) fr[i] = (uint32_t)row_frame(st, row0 + i, (int32_t)fr[i]);
+  }
   bool nan_t = false, nan_v = false;
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
@@ -396,7 +481,7 @@ __device__ __forceinline__ void select_slice(const float* __restrict__ tar, cons
   if (broken) {
     // metadata breaks the cache invariants: report, and keep rows 0..C-1 in place
     if (tid == 0) raise_error(err, any_bad ? 2u : 4u);
-    for (int32_t j = tid; j < budget; j += (int32_t)blockDim.x) put(j, j);
+    keep_first_rows<NT>(budget, sh, out);
     return;
   }
   const int32_t b_tar = max(0, tar_total - n_recent);
@@ -427,7 +512,7 @@ __device__ __forceinline__ void select_slice(const float* __restrict__ tar, cons
   int32_t total;
   int32_t pos = block_exclusive_scan<NT>(__popcll(kept), sh.wave_tot[2], &total);
   if (total != budget && tid == 0) raise_error(err, 16u);  // only reachable with NaN keys
-  write_keep<NT, RPT>(kept, pos, budget, row0, sh, put);
+  write_keep<NT, RPT>(kept, pos, budget, row0, sh, out);
 }
 
 // ---------------------------------------------------------------- Uniform Select
@@ -447,18 +532,23 @@ __device__ __forceinline__ bool uniform_taken(int64_t rank, int64_t k, int64_t q
   return (rank * k + q - 1) / q * q < (rank + 1) * k;
 }
 
-template <int NT, int RPT, bool VEC>
+template <int NT, int RPT, bool VEC, class ST, class EM>
 __device__ __forceinline__ void uniform_slice(const int32_t* __restrict__ frame_idx, int64_t S, int32_t n,
                                               int32_t budget, int32_t r, int32_t* __restrict__ keep_idx,
                                               uint32_t* err, int64_t slice, int32_t heads, uint32_t* __restrict__ zero,
-                                              int32_t zero_per_slice, SelShared<NT>& sh) {
+                                              int32_t zero_per_slice, SelShared<NT>& sh, const ST& st, const EM& em) {
   constexpr int NW = NT / kWave;
   const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
   const int64_t base = slice * S;
   const int64_t row0 = (int64_t)tid * RPT;
-  int32_t* keep = keep_idx + slice * budget;
-  auto put = [&](int32_t j, int32_t row) {
-    for (int32_t h = 0; h < heads; ++h) keep[(int64_t)h * budget + j] = row;
+  auto out = [&](int32_t lo, int32_t hi) {
+    if constexpr (ST::kNew) {
+      emit_rows<NT>(st, em, S, n, budget, slice, heads, lo, hi, sh.stage);
+    } else {
+      int32_t* keep = keep_idx + slice * budget;
+      for (int32_t j = threadIdx.x; j < hi - lo; j += (int32_t)blockDim.x)
+        for (int32_t h = 0; h < heads; ++h) keep[(int64_t)h * budget + lo + j] = sh.stage[j];
+    }
   };
   // no score kernel runs before this selection in a pass: it zeroes the
   // compaction flags of its slices (zero_per_slice words each) instead
@@ -470,12 +560,16 @@ __device__ __forceinline__ void uniform_slice(const int32_t* __restrict__ frame_
   uint32_t fr[RPT];
   load_row_run<RPT, VEC>(frame_idx + base, S, row0, fr);
   const __amdgpu_buffer_rsrc_t frs = buffer_rsrc(frame_idx + base, (uint32_t)(S * 4));
-  const int32_t last = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(frs, (uint32_t)(n - 1) * 4u, 0, 0);
-  const int32_t before = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(
-      frs, (uint32_t)max(row0 - 1, (int64_t)0) * 4u, 0, 0);
+  const int32_t last = row_frame(st, n - 1, (int32_t)__builtin_amdgcn_raw_buffer_load_b32(frs, (uint32_t)(n - 1) * 4u, 0, 0));
+  const int32_t before = row_frame(st, row0 - 1, (int32_t)__builtin_amdgcn_raw_buffer_load_b32(
+                                                     frs, (uint32_t)max(row0 - 1, (int64_t)0) * 4u, 0, 0));
   const int64_t thr = (int64_t)last - r + 1;
   uint64_t valid = 0, recent = 0, start = 0;
-  bool bad = heads > 1 && heads_differ<RPT, VEC>(frame_idx + base, S, heads, row0, n, fr);
+  bool bad = heads > 1 && heads_differ<RPT, VEC>(frame_idx + base, S, heads, row0, stored_rows(st, n), fr);
+  if constexpr (ST::kNew) {
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) fr[i] = (uint32_t)row_frame(st, row0 + i, (int32_t)fr[i]);
+  }
   int32_t prev = before;
 #pragma unroll
   for (int i = 0; i < RPT; ++i) {
@@ -501,7 +595,7 @@ __device__ __forceinline__ void uniform_slice(const int32_t* __restrict__ frame_
   const int32_t n_recent = n - n_past;
   if (any_bad || n_recent > budget) {
     if (tid == 0) raise_error(err, any_bad ? 2u : 4u);
-    for (int32_t j = tid; j < budget; j += (int32_t)blockDim.x) put(j, j);
+    keep_first_rows<NT>(budget, sh, out);
     return;
   }
   const uint64_t past = valid & ~recent;
@@ -540,32 +634,32 @@ __device__ __forceinline__ void uniform_slice(const int32_t* __restrict__ frame_
   const uint64_t kept = recent | pick;
   int32_t total;
   int32_t pos = block_exclusive_scan<NT>(__popcll(kept), sh.wave_tot[2], &total);
-  write_keep<NT, RPT>(kept, pos, budget, row0, sh, put);
+  write_keep<NT, RPT>(kept, pos, budget, row0, sh, out);
 }
 
 // grid: one block per group of `heads` consecutive slices (heads > 1: every
 // head must hold the same frame ids and receives the same keep set).
 // zero (may be null): zero_per_slice words per slice to clear
-template <int NT, int RPT, bool VEC>
+template <int NT, int RPT, bool VEC, class ST, class EM>
 __global__ __launch_bounds__(NT) void k_select_uniform(const int32_t* __restrict__ frame_idx, int64_t S, int32_t n,
                                                        int32_t budget, int32_t r, int32_t* __restrict__ keep_idx,
                                                        uint32_t* err, int32_t heads, uint32_t* __restrict__ zero,
-                                                       int32_t zero_per_slice) {
+                                                       int32_t zero_per_slice, ST st, EM em) {
   __shared__ SelShared<NT> sh;
   uniform_slice<NT, RPT, VEC>(frame_idx, S, n, budget, r, keep_idx, err, (int64_t)blockIdx.x * heads, heads, zero,
-                              zero_per_slice, sh);
+                              zero_per_slice, sh, st, em);
 }
 
 // grid: one block per group of `heads` consecutive slices
-template <int NT, int RPT, bool VEC>
+template <int NT, int RPT, bool VEC, class ST, class EM>
 __global__ __launch_bounds__(NT) void k_select(const float* __restrict__ tar, const float* __restrict__ van,
                                                const int32_t* __restrict__ frame_idx, int64_t S, int32_t n,
                                                int32_t budget, int32_t tar_total, int32_t r,
                                                int32_t* __restrict__ keep_idx, uint32_t* err, int32_t heads,
-                                               uint32_t tflip, uint32_t vflip) {
+                                               uint32_t tflip, uint32_t vflip, ST st, EM em) {
   __shared__ SelShared<NT> sh;
   select_slice<NT, RPT, VEC>(tar, van, frame_idx, S, n, budget, tar_total, r, keep_idx, err,
-                             (int64_t)blockIdx.x * heads, heads, tflip, vflip, sh);
+                             (int64_t)blockIdx.x * heads, heads, tflip, vflip, sh, st, em);
 }
 
 }  // namespace ipv

@@ -1,0 +1,98 @@
+"""Passes over resident frames (ipv_ckv_stream) against the loop that appends
+every frame and compacts at every pass (ipv_ckv_step): caches, metadata and
+row counts, and the last pass's scores and keep sets, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from paper_2506_15745_amd import ipv
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+#  L, H, D, grid, rows a frame, entry rows per stream, frames, cap, budget, r, capacity, dtype, mode, pooling
+CASES = {
+    # entry rows and budget over several 512-row chunks: the gather's waits
+    "entry-chunks": (2, 2, 128, (7, 7), 49, (1100, 1100), 60, 2000, 1600, 4, 2052, "bf16", 0, None),
+    # every pass brings one or two frames: the window reaches into old rows, places read through the index
+    "few-new-frames": (1, 2, 64, (5, 5), 25, (0, 75), 40, 301, 270, 3, 333, "f32", 0, None),
+    # frames of fewer rows than the grid; streams with passes at different frames; one that never fires
+    "partial-frames": (2, 1, 128, (6, 7), 31, (0, 310, 42), 37, 700, 400, 4, 731, "bf16", 0, None),
+    "pooled": (4, 2, 64, (4, 4), 16, (0, 64), 30, 130, 70, 2, 146, "bf16", ipv.VAN_REVERSE, (0.3, 0.5, 0.7)),
+    "adjacent": (2, 2, 128, (9, 13), 117, (234,), 40, 1300, 700, 3, 1417, "bf16", ipv.TAR_ADJACENT, None),
+    "adjacent-shared-f32": (2, 4, 256, (3, 5), 15, (15,), 40, 150, 91, 2, 165, "f32",
+                            ipv.TAR_ADJACENT | ipv.HEAD_SHARED, None),
+    "adjacent-pooled": (2, 2, 32, (4, 4), 16, (0,), 40, 130, 70, 2, 146, "bf16", ipv.TAR_ADJACENT, (0.3, 0.5, 0.7)),
+    "uniform": (2, 2, 128, (7, 7), 49, (0, 600), 60, 1300, 700, 2, 1349, "bf16", ipv.UNIFORM_SELECT, None),
+    "uniform-shared": (2, 2, 64, (7, 7), 49, (98,), 60, 1300, 700, 2, 1349, "f32",
+                       ipv.UNIFORM_SELECT | ipv.HEAD_SHARED, None),
+    # budget equal to the cap: one pass, at the last frame
+    "budget-is-cap": (1, 1, 32, (4, 4), 16, (3,), 8, 128, 128, 2, 144, "bf16", 0, None),
+    # more rows than 32 a selection thread, keep set over several stages
+    "long": (1, 1, 32, (14, 14), 196, (0,), 180, 33000, 30000, 5, 33196, "bf16", 0, None),
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+@pytest.mark.parametrize("cut", [0, 1])
+def test_stream_passes_equal_step_by_step(name, cut):
+    L, H, D, (gh, gw), rows, entry, frames, cap, budget, r, S, dtype, mode, tau = CASES[name]
+    p, B = gh * gw, len(entry)
+    sd, kind, bits = (synth.BF16, "bf16", torch.int16) if dtype == "bf16" else (synth.F32, "raw", torch.int32)
+    sigma = (0.1, 0.35, 0.55, 1.0) if tau else (0.5,)
+    src = [synth.fresh_cache(900 + b, L, H, frames * p, D, gh, gw, frames * p, sd, synth.RhoSpec(0.0, 0.95, 0.2), sigma)
+           for b in range(B)]
+    old = [synth.fresh_cache(950 + b, L, H, S, D, gh, gw, max(n, 1), sd, synth.RhoSpec(0.0, 0.95), sigma)
+           for b, n in enumerate(entry)]
+    fr_of = lambda a, f: np.stack([getattr(s, a)[:, :, f * p:f * p + rows] for s in src])  # noqa: E731
+    fK = P.to_device(np.ascontiguousarray(np.stack([fr_of("K", f) for f in range(frames)])), kind)
+    fV = P.to_device(np.ascontiguousarray(np.stack([fr_of("V", f) for f in range(frames)])), kind)
+
+    def fresh():
+        K = torch.zeros((B, L, H, S, D), dtype=torch.bfloat16 if dtype == "bf16" else torch.float32, device="cuda:0")
+        V = torch.zeros_like(K)
+        fr = torch.full((B, L, H, S), -1, dtype=torch.int32, device="cuda:0")
+        pa = torch.full_like(fr, -1)
+        for b, n in enumerate(entry):
+            if n:
+                K[b, :, :, :n] = P.to_device(np.ascontiguousarray(old[b].K[:, :, :n]), kind)
+                V[b, :, :, :n] = P.to_device(np.ascontiguousarray(old[b].V[:, :, :n]), kind)
+                fr[b, :, :, :n] = P.to_device(np.ascontiguousarray(old[b].frame_idx[:, :, :n] - 1000))
+                pa[b, :, :, :n] = P.to_device(np.ascontiguousarray(old[b].patch_idx[:, :, :n]))
+        return K, V, fr, pa, ipv.Compressor(K, gh, gw, budget)
+
+    args = (cap, budget, 0.5, r, tau)
+    if name == "budget-is-cap":  # the count after the pass admits no further frame
+        frames = -(-(cap - entry[0]) // rows)
+    K1, V1, f1, p1, c1 = fresh()
+    n1, passes1 = list(entry), [0] * B
+    at = [0] * B  # rows at each stream's last pass
+    for f in range(frames):
+        before = n1
+        n1, fired = ipv.ipv_ckv_step(K1, V1, f1, p1, n1, fK[f], fV[f], f, 0, *args, c1.tar, c1.van, c1.keep_idx, c1.ws,
+                                     gh, gw, mode=mode)
+        for b in range(B):
+            passes1[b] += int(fired[b])
+            at[b] = before[b] + rows if fired[b] else at[b]
+    K2, V2, f2, p2, c2 = fresh()
+    n2, passes2 = list(entry), [0] * B
+    cuts = [0, frames // 3, frames // 3 + 1, frames] if cut else [0, frames]
+    for a, b in zip(cuts, cuts[1:]):
+        n2, ps = ipv.ipv_ckv_stream(K2, V2, f2, p2, n2, fK[a:b], fV[a:b], a, *args, c2.tar, c2.van, c2.keep_idx, c2.ws,
+                                    gh, gw, mode=mode)
+        passes2 = [x + y for x, y in zip(passes2, ps)]
+    torch.cuda.synchronize()
+    assert c1.device_errors() == 0 and c2.device_errors() == 0
+    assert n2 == n1 and passes2 == passes1 and max(passes1) >= 1
+    for b in range(B):
+        m = n1[b]
+        for x, y in ((K1, K2), (V1, V2)):
+            assert torch.equal(x[b, :, :, :m].view(bits), y[b, :, :, :m].view(bits))
+        assert torch.equal(f1[b, :, :, :m], f2[b, :, :, :m]) and torch.equal(p1[b, :, :, :m], p2[b, :, :, :m])
+        if passes1[b]:
+            assert torch.equal(c1.keep_idx[b], c2.keep_idx[b])
+            if not mode & ipv.UNIFORM_SELECT:
+                for x, y in ((c1.tar, c2.tar), (c1.van, c2.van)):
+                    assert torch.equal(x[b, :, :, :at[b]].view(torch.int32), y[b, :, :, :at[b]].view(torch.int32))
+    print(name, "passes", passes1, "rows", n1, flush=True)
