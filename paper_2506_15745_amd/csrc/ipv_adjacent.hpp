@@ -148,13 +148,16 @@ __device__ __forceinline__ void prev_rows_block(int64_t slice, const int32_t* __
 }
 
 // grid: one block per slice
+template <class ST>
 __global__ __launch_bounds__(kPrevThreads) void k_prev_rows(const int32_t* __restrict__ frame_idx,
                                                             const int32_t* __restrict__ patch_idx, int64_t S,
                                                             int32_t n, int32_t r, int32_t p,
                                                             int32_t* __restrict__ prev,
                                                             int32_t* __restrict__ first_recent, uint32_t* err,
-                                                            uint32_t* __restrict__ zero, int32_t zero_per_slice) {
-  prev_rows_block(blockIdx.x, frame_idx, patch_idx, S, n, r, p, prev, first_recent, err, zero, zero_per_slice, Whole{});
+                                                            uint32_t* __restrict__ zero, int32_t zero_per_slice, ST st) {
+  n = slice_rows(st, n, blockIdx.x);
+  if (ST::kRagged && n == 0) return;
+  prev_rows_block(blockIdx.x, frame_idx, patch_idx, S, n, r, p, prev, first_recent, err, zero, zero_per_slice, st);
 }
 
 // The prev-row walk and the VaN tiles of the sweep in one launch (VaN needs
@@ -163,14 +166,16 @@ __global__ __launch_bounds__(kPrevThreads) void k_prev_rows(const int32_t* __res
 // hold four VaN tiles of 256 threads each, XCD-mapped like the sweep.
 // prev_padded is a multiple of 8, so tile block i + prev_padded runs on XCD
 // i % 8.
-template <typename T, int D>
+template <typename T, int D, class ST>
 __global__ __launch_bounds__(kPrevThreads) void k_prev_van(const T* __restrict__ V, const int32_t* __restrict__ frame_idx,
     const int32_t* __restrict__ patch_idx, int64_t S, int32_t n, int32_t r, int32_t p, int32_t* __restrict__ prev,
     int32_t* __restrict__ first_recent, uint32_t* err, uint32_t* __restrict__ zero, int32_t zero_per_slice,
-    uint32_t prev_padded, uint32_t slices, float* __restrict__ van, TileGrid g) {
+    uint32_t prev_padded, uint32_t slices, float* __restrict__ van, TileGrid g, ST st) {
   if (blockIdx.x < prev_padded) {
-    if (blockIdx.x < slices)
-      prev_rows_block(blockIdx.x, frame_idx, patch_idx, S, n, r, p, prev, first_recent, err, zero, zero_per_slice, Whole{});
+    if (blockIdx.x >= slices) return;
+    n = slice_rows(st, n, blockIdx.x);
+    if (ST::kRagged && n == 0) return;
+    prev_rows_block(blockIdx.x, frame_idx, patch_idx, S, n, r, p, prev, first_recent, err, zero, zero_per_slice, st);
     return;
   }
   using C = SweepCfg<T, D>;
@@ -179,9 +184,12 @@ __global__ __launch_bounds__(kPrevThreads) void k_prev_van(const T* __restrict__
   if (logical >= g.n_work) return;
   const uint32_t tile = fast_div(logical, g.col_blocks);
   const uint32_t colblock = logical - tile * g.col_blocks.d;
-  const uint32_t slice = fast_div(tile, g.frame_blocks);
-  const uint32_t f0 = (tile - slice * g.frame_blocks.d) * C::U;
-  sweep_tile<T, D, false, true>(V, V, patch_idx, S, n, p, nullptr, n, nullptr, van, err, slice, f0, colblock,
+  const uint32_t place = fast_div(tile, g.frame_blocks);
+  const uint32_t f0 = (tile - place * g.frame_blocks.d) * C::U;
+  const uint32_t slice = tile_slice(st, place);
+  uint32_t rows = (uint32_t)n;
+  if (no_tile(st, slice, rows, f0 * (uint32_t)p)) return;
+  sweep_tile<T, D, false, true>(V, V, patch_idx, S, rows, p, nullptr, rows, nullptr, van, err, slice, f0, colblock,
                                 threadIdx.x % 256u);
 }
 
@@ -191,18 +199,21 @@ __global__ __launch_bounds__(kPrevThreads) void k_prev_van(const T* __restrict__
 // per row. K[x] (past rows only) loads go out with the prev(x) loads;
 // K[prev(x)] follows once prev(x) is known. Branch-free buffer loads: a lane
 // with nothing to read uses an offset past the end.
-template <typename T, int D>
+template <typename T, int D, class ST>
 __global__ __launch_bounds__(256) void k_adjacent_sweep(const T* __restrict__ K, const int32_t* __restrict__ prev,
                                                         int64_t S, int32_t n, const int32_t* __restrict__ first_recent,
                                                         float* __restrict__ tar, int32_t blocks_per_slice,
-                                                        uint32_t n_work) {
+                                                        uint32_t n_work, ST st) {
   constexpr int EPL = Lane<T>::EPL, LPR = D / EPL, GROUPS = 256 / LPR, U = 4;
   constexpr uint32_t kSkip = 0xfffffff0u;
   constexpr uint32_t RB = D * (uint32_t)sizeof(T);
   const uint32_t logical = xcd_logical_id(blockIdx.x, gridDim.x);
   if (logical >= n_work) return;
-  const int64_t slice = logical / blocks_per_slice;
+  const int64_t slice = tile_slice(st, logical / blocks_per_slice);
   const int64_t r0 = (int64_t)(logical % blocks_per_slice) * GROUPS * U;
+  uint32_t rows = (uint32_t)n;
+  if (no_tile(st, (uint32_t)slice, rows, (uint32_t)r0)) return;
+  n = (int32_t)rows;
   const int tid = threadIdx.x, g = tid / LPR, lane = tid % LPR;
   const int64_t base = slice * S;
   const int32_t rec = first_recent[slice];

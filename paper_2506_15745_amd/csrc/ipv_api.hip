@@ -147,6 +147,10 @@ TileGrid tile_grid(int32_t col_blocks, int32_t frame_blocks, uint32_t work, uint
   return TileGrid{make_fastdiv((uint32_t)col_blocks), make_fastdiv((uint32_t)frame_blocks), work, blocks};
 }
 
+// slices of the tile grid (Ragged: padded to a whole number for every XCD)
+uint32_t grid_slices(const Dims& d, const Whole&) { return (uint32_t)d.slices; }
+uint32_t grid_slices(const Dims&, const Ragged& rows) { return 8u * rows.per_xcd.d; }
+
 uint32_t pad8(uint32_t x) { return (x + 7u) / 8u * 8u; }
 
 // ------------------------------------------------------------ launchers
@@ -163,10 +167,11 @@ ipv_status no_mark() { return IPV_OK; }
 // cv_tau (may be null): with both scores and the recent-key table, the TaR
 // launch also computes the pooling CV and window of every (stream, layer)
 // (k_pool_apply must follow); ignored otherwise.
-template <typename T, int D, typename Between>
+template <typename T, int D, class ST, typename Between>
 ipv_status run_scores(const Dims& d, const void* K, const void* V, const int32_t* fr, const int32_t* pa, int32_t n,
                       int32_t r, float* tar, float* van, void* ws, hipStream_t st, Between between,
-                      int64_t zero_chunks, bool adjacent, const double* cv_tau) {
+                      int64_t zero_chunks, bool adjacent, const double* cv_tau, const ST& rows) {
+  const uint32_t tile_slices = grid_slices(d, rows);
   const bool do_tar = K != nullptr, do_van = V != nullptr;
   uint32_t* zero = zero_chunks > 0 ? ws_flags(ws, d) : nullptr;
   const int32_t zero_per_slice = (int32_t)(compact_parts(d) * walk_words(zero_chunks));
@@ -176,23 +181,23 @@ ipv_status run_scores(const Dims& d, const void* K, const void* V, const int32_t
       using C = SweepCfg<T, D>;
       const int32_t col_blocks = (int32_t)((d.p + C::GROUPS - 1) / C::GROUPS);
       const int32_t frame_blocks = (int32_t)(((n + d.p - 1) / d.p + C::U - 1) / C::U);
-      const uint32_t work = (uint32_t)(d.slices * frame_blocks * col_blocks);
+      const uint32_t work = tile_slices * (uint32_t)(frame_blocks * col_blocks);
       const uint32_t prev_padded = pad8((uint32_t)d.slices);
-      k_prev_van<T, D><<<dim3(prev_padded + pad8((work + 3) / 4)), dim3(kPrevThreads), 0, st>>>(
+      k_prev_van<T, D, ST><<<dim3(prev_padded + pad8((work + 3) / 4)), dim3(kPrevThreads), 0, st>>>(
           static_cast<const T*>(V), fr, pa, d.S, n, r, (int32_t)d.p, ws_prev(ws), ws_first(ws, d), err_word(ws),
           zero, zero_per_slice, prev_padded, (uint32_t)d.slices, van,
-          tile_grid(col_blocks, frame_blocks, work, pad8((work + 3) / 4)));
+          tile_grid(col_blocks, frame_blocks, work, pad8((work + 3) / 4)), rows);
     } else {
-      k_prev_rows<<<dim3((uint32_t)d.slices), dim3(kPrevThreads), 0, st>>>(
-          fr, pa, d.S, n, r, (int32_t)d.p, ws_prev(ws), ws_first(ws, d), err_word(ws), zero, zero_per_slice);
+      k_prev_rows<ST><<<dim3((uint32_t)d.slices), dim3(kPrevThreads), 0, st>>>(
+          fr, pa, d.S, n, r, (int32_t)d.p, ws_prev(ws), ws_first(ws, d), err_word(ws), zero, zero_per_slice, rows);
     }
     IPV_TRY(between());
     // then the TaR rows
     constexpr int ROWS = 256 / (D / Lane<T>::EPL) * 4;
     const int32_t bps = (n + ROWS - 1) / ROWS;
-    const uint32_t work = (uint32_t)(d.slices * bps);
-    k_adjacent_sweep<T, D><<<dim3(pad8(work)), dim3(256), 0, st>>>(static_cast<const T*>(K), ws_prev(ws), d.S, n,
-                                                                   ws_first(ws, d), tar, bps, work);
+    const uint32_t work = tile_slices * (uint32_t)bps;
+    k_adjacent_sweep<T, D, ST><<<dim3(pad8(work)), dim3(256), 0, st>>>(static_cast<const T*>(K), ws_prev(ws), d.S, n,
+                                                                       ws_first(ws, d), tar, bps, work, rows);
     return launched();
   }
   constexpr int GROUPS = 256 / (D / Lane<T>::EPL);
@@ -202,56 +207,55 @@ ipv_status run_scores(const Dims& d, const void* K, const void* V, const int32_t
   using C = SweepCfg<T, D>;
   const int32_t col_blocks = (int32_t)((d.p + C::GROUPS - 1) / C::GROUPS);
   const int32_t frame_blocks = (int32_t)(((n + d.p - 1) / d.p + C::U - 1) / C::U);
-  const uint32_t work = (uint32_t)(d.slices * frame_blocks * col_blocks);
+  const uint32_t work = tile_slices * (uint32_t)(frame_blocks * col_blocks);
   const dim3 grid(pad8(work)), block(256);
   const T* k = static_cast<const T*>(K);
   const T* v = static_cast<const T*>(V);
   int32_t* first = ws_first(ws, d);
-  // rows certainly before the recent window (it holds at most r * p rows)
-  const int32_t sure_past = (int32_t)std::max<int64_t>(0, (int64_t)n - (int64_t)r * d.p);
+  const int32_t window = (int32_t)((int64_t)r * d.p);  // most rows the recent window can hold
   if (do_tar && do_van) {
     // table and VaN tiles in one launch, then the TaR tiles
     const uint32_t table_padded = pad8(table_real);
-    k_table_van<T, D><<<dim3(table_padded + pad8(work)), block, lds, st>>>(
+    k_table_van<T, D, ST><<<dim3(table_padded + pad8(work)), block, lds, st>>>(
         k, v, fr, pa, d.S, n, r, (int32_t)d.p, blocks, table_padded, table_real, ws_table(ws), first, err_word(ws),
-        zero, zero_per_slice, van, tile_grid(col_blocks, frame_blocks, work, pad8(work)));
+        zero, zero_per_slice, van, tile_grid(col_blocks, frame_blocks, work, pad8(work)), rows);
     IPV_TRY(between());
     if (cv_tau) {
       const uint32_t cv_real = (uint32_t)(d.B * d.L), cv_padded = pad8(cv_real);
-      k_tar_sweep_cv<T, D><<<dim3(cv_padded + pad8(work)), block, 0, st>>>(
+      k_tar_sweep_cv<T, D, ST><<<dim3(cv_padded + pad8(work)), block, 0, st>>>(
           k, pa, d.S, n, (int32_t)d.p, ws_table(ws), first, tar, err_word(ws),
-          tile_grid(col_blocks, frame_blocks, work, pad8(work)), sure_past, van, (int32_t)d.H, cv_tau[0], cv_tau[1],
-          cv_tau[2], ws_pool(ws, d), cv_padded, cv_real);
+          tile_grid(col_blocks, frame_blocks, work, pad8(work)), window, van, (int32_t)d.H, cv_tau[0], cv_tau[1],
+          cv_tau[2], ws_pool(ws, d), cv_padded, cv_real, rows);
       return launched();
     }
-    k_score_sweep<T, D, true, false><<<grid, block, 0, st>>>(k, v, pa, d.S, n, (int32_t)d.p, ws_table(ws), first,
+    k_score_sweep<T, D, true, false, ST><<<grid, block, 0, st>>>(k, v, pa, d.S, n, (int32_t)d.p, ws_table(ws), first,
                                                              tar, van, err_word(ws),
-                                                             tile_grid(col_blocks, frame_blocks, work, pad8(work)), sure_past);
+                                                             tile_grid(col_blocks, frame_blocks, work, pad8(work)), window, rows);
     return launched();
   }
   if (do_tar)
-    k_recent_table<T, D><<<dim3(table_real), block, lds, st>>>(k, fr, pa, d.S, n, r, (int32_t)d.p, blocks,
-                                                               ws_table(ws), first, err_word(ws), zero,
-                                                               zero_per_slice);
+    k_recent_table<T, D, ST><<<dim3(table_real), block, lds, st>>>(k, fr, pa, d.S, n, r, (int32_t)d.p, blocks,
+                                                                   ws_table(ws), first, err_word(ws), zero,
+                                                                   zero_per_slice, rows);
   IPV_TRY(between());
   if (do_tar)
-    k_score_sweep<T, D, true, false><<<grid, block, 0, st>>>(k, v, pa, d.S, n, (int32_t)d.p, ws_table(ws), first,
+    k_score_sweep<T, D, true, false, ST><<<grid, block, 0, st>>>(k, v, pa, d.S, n, (int32_t)d.p, ws_table(ws), first,
                                                              tar, van, err_word(ws),
-                                                             tile_grid(col_blocks, frame_blocks, work, pad8(work)), sure_past);
+                                                             tile_grid(col_blocks, frame_blocks, work, pad8(work)), window, rows);
   else
-    k_score_sweep<T, D, false, true><<<grid, block, 0, st>>>(k, v, pa, d.S, n, (int32_t)d.p, ws_table(ws), first,
+    k_score_sweep<T, D, false, true, ST><<<grid, block, 0, st>>>(k, v, pa, d.S, n, (int32_t)d.p, ws_table(ws), first,
                                                              tar, van, err_word(ws),
-                                                             tile_grid(col_blocks, frame_blocks, work, pad8(work)), n);
+                                                             tile_grid(col_blocks, frame_blocks, work, pad8(work)), 0, rows);
   return launched();
 }
 
-template <typename Between = ipv_status (*)()>
+template <class ST, typename Between = ipv_status (*)()>
 ipv_status scores(const Dims& d, const void* K, const void* V, const int32_t* fr, const int32_t* pa, int32_t n,
-                  int32_t r, float* tar, float* van, void* ws, hipStream_t st, Between between = no_mark,
+                  const ST& rows, int32_t r, float* tar, float* van, void* ws, hipStream_t st, Between between = no_mark,
                   int64_t zero_chunks = 0, bool adjacent = false, const double* cv_tau = nullptr) {
 #define IPV_SCORES(T, DD)                                                                                        \
   if (d.D == DD)                                                                                                 \
-    return run_scores<T, DD>(d, K, V, fr, pa, n, r, tar, van, ws, st, between, zero_chunks, adjacent, cv_tau);
+    return run_scores<T, DD>(d, K, V, fr, pa, n, r, tar, van, ws, st, between, zero_chunks, adjacent, cv_tau, rows);
   if (d.dtype == IPV_BF16) {
     IPV_SCORES(uint16_t, 32) IPV_SCORES(uint16_t, 64) IPV_SCORES(uint16_t, 128) IPV_SCORES(uint16_t, 256)
   } else {
@@ -262,12 +266,12 @@ ipv_status scores(const Dims& d, const void* K, const void* V, const int32_t* fr
 }
 
 // cv_done: the TaR launch has computed the windows already (k_tar_sweep_cv)
-template <class ST = Whole>
+template <class ST>
 ipv_status pool_d(const Dims& d, const double* tau, float* van, const int32_t* fr, const int32_t* pa, int32_t n,
-                  int32_t* pool_out, void* ws, hipStream_t st, bool cv_done = false, const ST& rows = ST{}) {
+                  const ST& rows, int32_t* pool_out, void* ws, hipStream_t st, bool cv_done = false) {
   if (!cv_done)
     k_pool_cv<<<dim3((uint32_t)(d.B * d.L)), dim3(kPoolThreads), 0, st>>>(van, d.S, n, (int32_t)d.H, tau[0], tau[1],
-                                                                          tau[2], ws_pool(ws, d), pool_out);
+                                                                          tau[2], ws_pool(ws, d), pool_out, rows);
   k_pool_apply<<<dim3((uint32_t)d.slices), dim3(kPoolThreads), 0, st>>>(
       van, fr, pa, d.S, n, (int32_t)d.H, d.gh, d.gw, ws_pool(ws, d), make_fastdiv((uint32_t)d.p),
       make_fastdiv((uint32_t)d.gw), rows);
@@ -329,10 +333,10 @@ ipv_status run_uniform(const Dims& d, const int32_t* fr, int32_t n, int32_t budg
 
 // zero / zero_per_slice: as for run_uniform (used by Uniform Select only).
 // rows / em: a Stretch and its Emit for a pass over rows outside the cache.
-template <class ST = Whole, class EM = NoEmit>
-ipv_status select(const Dims& d, const float* tar, const float* van, const int32_t* fr, int32_t n, int32_t budget,
-                  int32_t tar_total, int32_t r, int32_t* keep, uint32_t* err, hipStream_t st, uint32_t mode,
-                  uint32_t* zero = nullptr, int32_t zero_per_slice = 0, const ST& rows = ST{}, const EM& em = EM{}) {
+template <class ST, class EM = NoEmit>
+ipv_status select(const Dims& d, const float* tar, const float* van, const int32_t* fr, int32_t n, const ST& rows,
+                  int32_t budget, int32_t tar_total, int32_t r, int32_t* keep, uint32_t* err, hipStream_t st,
+                  uint32_t mode, uint32_t* zero = nullptr, int32_t zero_per_slice = 0, const EM& em = EM{}) {
   const int32_t rpt = (n + kSelThreads - 1) / kSelThreads;
   // A block of up to 8 rows a thread (832 threads for 6272 rows) holds a CU
   // alone; with more blocks than CUs, 16 rows a thread (half the threads)
@@ -365,9 +369,9 @@ int64_t compact_chunks(int32_t budget) { return (budget + kCompactRows - 1) / kC
 
 // flags_zeroed: an earlier kernel of the pass (the table or prev-row launch, or
 // the uniform selection) has zeroed the flags already
-template <int RB>
-ipv_status run_compact(const Dims& d, void* K, void* V, int32_t* fr, int32_t* pa, int32_t n, const int32_t* keep,
-                       int32_t budget, void* ws, hipStream_t st, bool flags_zeroed) {
+template <int RB, class ST>
+ipv_status run_compact(const Dims& d, void* K, void* V, int32_t* fr, int32_t* pa, int32_t n, const ST& rows,
+                       const int32_t* keep, int32_t budget, void* ws, hipStream_t st, bool flags_zeroed) {
   using C = CompactCfg<RB, kCompactThreads, kCompactRows, kCompactColBytes>;
   const uint32_t chunks = (uint32_t)compact_chunks(budget);
   const int64_t total = d.slices * C::PARTS * chunks;
@@ -377,18 +381,19 @@ ipv_status run_compact(const Dims& d, void* K, void* V, int32_t* fr, int32_t* pa
   }
   k_compact<RB, kCompactThreads, kCompactRows, kCompactColBytes><<<dim3((uint32_t)total), dim3(kCompactThreads), 0, st>>>(
       static_cast<char*>(K), static_cast<char*>(V), fr, pa, d.S, n, budget, keep, err_word(ws), ws_flags(ws, d),
-      chunks, make_fastdiv((uint32_t)(d.slices * C::PARTS)));
+      chunks, make_fastdiv((uint32_t)(d.slices * C::PARTS)), rows);
   return launched();
 }
 
-ipv_status compact(const Dims& d, void* K, void* V, int32_t* fr, int32_t* pa, int32_t n, const int32_t* keep,
-                   int32_t budget, void* ws, hipStream_t st, bool flags_zeroed = false) {
+template <class ST>
+ipv_status compact(const Dims& d, void* K, void* V, int32_t* fr, int32_t* pa, int32_t n, const ST& rows,
+                   const int32_t* keep, int32_t budget, void* ws, hipStream_t st, bool flags_zeroed = false) {
   switch (d.D * d.elem) {
-    case 64: return run_compact<64>(d, K, V, fr, pa, n, keep, budget, ws, st, flags_zeroed);
-    case 128: return run_compact<128>(d, K, V, fr, pa, n, keep, budget, ws, st, flags_zeroed);
-    case 256: return run_compact<256>(d, K, V, fr, pa, n, keep, budget, ws, st, flags_zeroed);
-    case 512: return run_compact<512>(d, K, V, fr, pa, n, keep, budget, ws, st, flags_zeroed);
-    case 1024: return run_compact<1024>(d, K, V, fr, pa, n, keep, budget, ws, st, flags_zeroed);
+    case 64: return run_compact<64>(d, K, V, fr, pa, n, rows, keep, budget, ws, st, flags_zeroed);
+    case 128: return run_compact<128>(d, K, V, fr, pa, n, rows, keep, budget, ws, st, flags_zeroed);
+    case 256: return run_compact<256>(d, K, V, fr, pa, n, rows, keep, budget, ws, st, flags_zeroed);
+    case 512: return run_compact<512>(d, K, V, fr, pa, n, rows, keep, budget, ws, st, flags_zeroed);
+    case 1024: return run_compact<1024>(d, K, V, fr, pa, n, rows, keep, budget, ws, st, flags_zeroed);
   }
   return IPV_ERR_SHAPE;
 }
@@ -529,11 +534,14 @@ ipv_status check_tau(const double* tau) {
 
 // ------------------------------------------------------------ per-stream row counts
 // Every call takes n_tokens as a host array of B row counts. The work is
-// launched once per maximal run of consecutive streams with the same count
-// (one run for a batch at one fill level); a stream with 0 rows is left alone.
-// A run is a contiguous sub-batch: the same layouts with fewer streams, so the
-// kernels see one count, and the runs reuse the workspace one after another
-// on the stream.
+// launched once per group of consecutive streams: a contiguous sub-batch, the
+// same layouts with fewer streams. A group of one count goes out as before the
+// counts came apart; streams of different counts share a launch (Ragged) when
+// its grid, made for the largest count, has rows for at least half of its
+// tiles, so that no short stream pays for a long one. A launch chain per count
+// leaves the chip idle between and within its launches: 16 caches of 28 slices
+// of up to 6272 rows at 11 fill levels took 880 us in 15 chains, 475 us in one. Groups reuse the
+// workspace one after another on the stream; a stream with 0 rows is left alone.
 Dims sub_batch(const Dims& d, int64_t nb) {
   Dims s = d;
   s.B = nb;
@@ -546,15 +554,35 @@ T* at_stream(T* p, int64_t b0, int64_t per_stream_elems) {
   return p ? p + b0 * per_stream_elems : p;
 }
 
-// fn(sub-batch dims, first stream, row count) for every run with a non-zero count
+// fn(sub-batch dims, first stream, largest row count, Whole or Ragged) for every group
 template <typename F>
-ipv_status for_each_run(const Dims& d, const int32_t* n_tokens, F fn) {
-  for (int64_t b = 0; b < d.B;) {
-    const int32_t n = n_tokens[b];
+ipv_status for_each_group(const Dims& d, const int32_t* n_tokens, F fn) {
+  auto run_end = [&](int64_t b) {
     int64_t e = b + 1;
-    while (e < d.B && n_tokens[e] == n) ++e;
-    if (n > 0) IPV_TRY(fn(sub_batch(d, e - b), b, n));
-    b = e;
+    while (e < d.B && n_tokens[e] == n_tokens[b]) ++e;
+    return e;
+  };
+  for (int64_t b = 0, e; b < d.B; b = e) {
+    e = run_end(b);
+    if (n_tokens[b] == 0) continue;
+    int64_t most = n_tokens[b], sum = most * (e - b), end = e;
+    while (end < d.B) {
+      const int64_t next = run_end(end), n = n_tokens[end];
+      most = std::max(most, n);
+      sum += n * (next - end);
+      if (next - b > kMaxRagged || most * (next - b) > 2 * sum) break;
+      end = next;
+      if (n > 0) e = end;  // no empty streams at the end of a group
+    }
+    const Dims s = sub_batch(d, e - b);
+    if (run_end(b) >= e) {
+      IPV_TRY(fn(s, b, n_tokens[b], Whole{}));
+      continue;
+    }
+    Ragged rows{make_fastdiv((uint32_t)(d.L * d.H)), make_fastdiv((uint32_t)((s.slices + 7) / 8)), (uint32_t)s.slices, {}};
+    int32_t n = 0;
+    for (int64_t i = b; i < e; ++i) n = std::max(n, rows.n[i - b] = n_tokens[i]);
+    IPV_TRY(fn(s, b, n, rows));
   }
   return IPV_OK;
 }
@@ -585,9 +613,10 @@ ipv_status check_pass_args(const Dims& d, const int32_t* n_tokens, int32_t budge
   return check_mode(mode);
 }
 
-// the whole pass on one run; events (may be NULL) as in ipv_compress_timed
-ipv_status compress_run(const Dims& d, void* K, void* V, int32_t* fr, int32_t* pa, int32_t n, int32_t budget,
-                        double alpha, int32_t r, uint32_t mode, const double* cv_tau, float* tar, float* van,
+// the whole pass on one group; events (may be NULL) as in ipv_compress_timed
+template <class ST>
+ipv_status compress_run(const Dims& d, void* K, void* V, int32_t* fr, int32_t* pa, int32_t n, const ST& rows,
+                        int32_t budget, double alpha, int32_t r, uint32_t mode, const double* cv_tau, float* tar, float* van,
                         int32_t* keep, void* ws, hipStream_t st, const ipv_events* events) {
   auto mark = [&](int i) -> ipv_status {
     if (!events || !events->at[i]) return IPV_OK;
@@ -601,17 +630,17 @@ ipv_status compress_run(const Dims& d, void* K, void* V, int32_t* fr, int32_t* p
   if (uniform)
     IPV_TRY(mark(1));
   else
-    IPV_TRY(scores(d, K, V, fr, pa, n, r, tar, van, ws, st, [&]() { return mark(1); }, compact_chunks(budget),
+    IPV_TRY(scores(d, K, V, fr, pa, n, rows, r, tar, van, ws, st, [&]() { return mark(1); }, compact_chunks(budget),
                    adjacent, cv_fused ? cv_tau : nullptr));
   IPV_TRY(mark(2));
-  if (cv_tau && !uniform) IPV_TRY(pool_d(d, cv_tau, van, fr, pa, n, nullptr, ws, st, cv_fused));
+  if (cv_tau && !uniform) IPV_TRY(pool_d(d, cv_tau, van, fr, pa, n, rows, nullptr, ws, st, cv_fused));
   IPV_TRY(mark(3));
   // the score launches zero the compaction's flags; without them the uniform selection does
-  IPV_TRY(select(d, tar, van, fr, n, budget, floor_share(alpha, budget), r, keep, err_word(ws), st, mode,
+  IPV_TRY(select(d, tar, van, fr, n, rows, budget, floor_share(alpha, budget), r, keep, err_word(ws), st, mode,
                  uniform ? ws_flags(ws, d) : nullptr,
                  (int32_t)(compact_parts(d) * walk_words(compact_chunks(budget)))));
   IPV_TRY(mark(4));
-  IPV_TRY(compact(d, K, V, fr, pa, n, keep, budget, ws, st, true));
+  IPV_TRY(compact(d, K, V, fr, pa, n, rows, keep, budget, ws, st, true));
   return mark(5);
 }
 
@@ -682,9 +711,9 @@ ipv_status ipv_tar_scores(const ipv_shape* shape, const void* K, const int32_t* 
   IPV_TRY(check_mode(mode));
   IPV_TRY(check_ws(d, ws, ws_bytes));
   const int64_t kb = kv_bytes_per_stream(d), rs = rows_per_stream(d);
-  return for_each_run(d, n_tokens, [&](const Dims& s, int64_t b0, int32_t n) {
+  return for_each_group(d, n_tokens, [&](const Dims& s, int64_t b0, int32_t n, const auto& rows) {
     return scores(s, static_cast<const char*>(K) + b0 * kb, nullptr, frame_idx + b0 * rs, patch_idx + b0 * rs, n,
-                  recent_frames, tar + b0 * rs, nullptr, ws, static_cast<hipStream_t>(stream), no_mark, 0,
+                  rows, recent_frames, tar + b0 * rs, nullptr, ws, static_cast<hipStream_t>(stream), no_mark, 0,
                   (mode & IPV_TAR_ADJACENT) != 0);
   });
 }
@@ -702,17 +731,20 @@ ipv_status ipv_van_scores(const ipv_shape* shape, const void* V, const int32_t* 
   IPV_TRY(check_ws(d, ws, ws_bytes));
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int64_t kb = kv_bytes_per_stream(d), rs = rows_per_stream(d);
-  return for_each_run(d, n_tokens, [&](const Dims& s, int64_t b0, int32_t n) -> ipv_status {
+  return for_each_group(d, n_tokens, [&](const Dims& s, int64_t b0, int32_t n, const auto& rows) -> ipv_status {
     const int32_t* fr = frame_idx + b0 * rs;
     const int32_t* pa = patch_idx + b0 * rs;
     float* vn = van + b0 * rs;
     int32_t* ps = at_stream(pool_size, b0, d.L);
-    IPV_TRY(scores(s, nullptr, static_cast<const char*>(V) + b0 * kb, fr, pa, n, 1, nullptr, vn, ws, st));
-    if (cv_tau) return pool_d(s, cv_tau, vn, fr, pa, n, ps, ws, st);
-    if (ps) {
-      const int64_t cnt = s.B * s.L;
-      k_fill_i32<<<dim3((uint32_t)((cnt + 255) / 256)), dim3(256), 0, st>>>(ps, cnt, 1);
-      return launched();
+    IPV_TRY(scores(s, nullptr, static_cast<const char*>(V) + b0 * kb, fr, pa, n, rows, 1, nullptr, vn, ws, st));
+    if (cv_tau) return pool_d(s, cv_tau, vn, fr, pa, n, rows, ps, ws, st);
+    // a window of 1 for every stream with rows
+    for (int64_t b = b0, e; ps && b < b0 + s.B; b = e) {
+      for (e = b + 1; e < b0 + s.B && (n_tokens[e] > 0) == (n_tokens[b] > 0);) ++e;
+      if (n_tokens[b] == 0) continue;
+      const int64_t cnt = (e - b) * d.L;
+      k_fill_i32<<<dim3((uint32_t)((cnt + 255) / 256)), dim3(256), 0, st>>>(pool_size + b * d.L, cnt, 1);
+      IPV_TRY(launched());
     }
     return IPV_OK;
   });
@@ -728,8 +760,8 @@ ipv_status ipv_select(const ipv_shape* shape, const float* tar, const float* van
   IPV_TRY(check_pass_args(d, n_tokens, budget, alpha, recent_frames, nullptr, mode));
   IPV_TRY(check_ws(d, ws, ws_bytes));
   const int64_t rs = rows_per_stream(d), ks = d.L * d.H * (int64_t)budget;
-  return for_each_run(d, n_tokens, [&](const Dims& s, int64_t b0, int32_t n) {
-    return select(s, at_stream(tar, b0, rs), at_stream(van, b0, rs), frame_idx + b0 * rs, n, budget,
+  return for_each_group(d, n_tokens, [&](const Dims& s, int64_t b0, int32_t n, const auto& rows) {
+    return select(s, at_stream(tar, b0, rs), at_stream(van, b0, rs), frame_idx + b0 * rs, n, rows, budget,
                   floor_share(alpha, budget),
                   recent_frames, keep_idx + b0 * ks, err_word(ws), static_cast<hipStream_t>(stream), mode);
   });
@@ -747,9 +779,9 @@ ipv_status ipv_compact(const ipv_shape* shape, void* K, void* V, int32_t* frame_
   IPV_TRY(check_counts(d, n_tokens, [&](int32_t n) { return budget < 1 || budget > n ? IPV_ERR_BUDGET : IPV_OK; }));
   IPV_TRY(check_ws(d, ws, ws_bytes));
   const int64_t kb = kv_bytes_per_stream(d), rs = rows_per_stream(d), ks = d.L * d.H * (int64_t)budget;
-  return for_each_run(d, n_tokens, [&](const Dims& s, int64_t b0, int32_t n) {
+  return for_each_group(d, n_tokens, [&](const Dims& s, int64_t b0, int32_t n, const auto& rows) {
     return compact(s, static_cast<char*>(K) + b0 * kb, static_cast<char*>(V) + b0 * kb, frame_idx + b0 * rs,
-                   patch_idx + b0 * rs, n, keep_idx + b0 * ks, budget, ws, static_cast<hipStream_t>(stream));
+                   patch_idx + b0 * rs, n, rows, keep_idx + b0 * ks, budget, ws, static_cast<hipStream_t>(stream));
   });
 }
 
@@ -869,15 +901,15 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
         if (!uniform)
           IPV_TRY(stretch_scores(s, k, v, sr, fr, pa, n, r, tr, vn, ws, st, chunks, adjacent,
                                  pool && !adjacent ? cv_tau : nullptr, l.passes > 0 && !pool));
-        if (pool) IPV_TRY(pool_d(s, cv_tau, vn, fr, pa, n, nullptr, ws, st, !adjacent, sr));
+        if (pool) IPV_TRY(pool_d(s, cv_tau, vn, fr, pa, n, sr, nullptr, ws, st, !adjacent));
         const Emit em{fr,
                       pa,
                       last ? places : keep,
                       last ? s.S : budget,
                       last || pool || uniform ? nullptr : vn,
                       last ? keep : nullptr};
-        IPV_TRY(select(s, tr, vn, fr, n, budget, floor_share(alpha, budget), r, keep, err_word(ws), st, mode,
-                       uniform && last ? ws_flags(ws, s) : nullptr, (int32_t)(compact_parts(s) * walk_words(chunks)), sr,
+        IPV_TRY(select(s, tr, vn, fr, n, sr, budget, floor_share(alpha, budget), r, keep, err_word(ws), st, mode,
+                       uniform && last ? ws_flags(ws, s) : nullptr, (int32_t)(compact_parts(s) * walk_words(chunks)),
                        em));
         if (last) IPV_TRY(stretch_gather(s, k, v, sr, places, entry[b0].n0, budget, ws, st));
         for (int64_t b = b0; b < e; ++b) {
@@ -940,9 +972,9 @@ ipv_status ipv_compress_timed(const ipv_shape* shape, void* K, void* V, int32_t*
                          cv_tau, tar, van, keep_idx));
   IPV_TRY(check_ws(d, ws, ws_bytes));
   const int64_t kb = kv_bytes_per_stream(d), rs = rows_per_stream(d), ks = d.L * d.H * (int64_t)budget;
-  return for_each_run(d, n_tokens, [&](const Dims& s, int64_t b0, int32_t n) {
+  return for_each_group(d, n_tokens, [&](const Dims& s, int64_t b0, int32_t n, const auto& rows) {
     return compress_run(s, static_cast<char*>(K) + b0 * kb, static_cast<char*>(V) + b0 * kb, frame_idx + b0 * rs,
-                        patch_idx + b0 * rs, n, budget, alpha, recent_frames, mode, cv_tau, at_stream(tar, b0, rs),
+                        patch_idx + b0 * rs, n, rows, budget, alpha, recent_frames, mode, cv_tau, at_stream(tar, b0, rs),
                         at_stream(van, b0, rs), keep_idx + b0 * ks, ws, static_cast<hipStream_t>(stream), events);
   });
 }

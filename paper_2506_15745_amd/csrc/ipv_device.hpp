@@ -275,9 +275,26 @@ __device__ __forceinline__ uint32_t fast_div(uint32_t x, const FastDiv& f) {
   return (t + ((x - t) >> f.s1)) >> f.s2;
 }
 
-// Where the rows of a launch's slices are. Whole: every row is in the cache.
+// Where the rows of a launch's slices are. Whole: every row is in the cache,
+// the same number in every slice.
 struct Whole {
-  static constexpr bool kNew = false;
+  static constexpr bool kNew = false, kRagged = false;
+};
+
+// Every row is in the cache, streams hold row counts of their own (0: the
+// stream is left alone); a launch's `n` is then the largest count and its grid
+// is made for that. The counts travel in the kernel arguments (256 bytes, one
+// scalar load a block), so nothing is copied to the GPU and a launch can be
+// captured. Slices are dealt over the XCDs one by one (slice 8b + a to XCD a)
+// instead of in runs: streams of different lengths would otherwise leave some
+// XCDs without tiles while others still stream.
+constexpr int kMaxRagged = 64;
+struct Ragged {
+  static constexpr bool kNew = false, kRagged = true;
+  FastDiv per_stream;  // slices per stream
+  FastDiv per_xcd;     // ceil(slices / 8)
+  uint32_t slices;
+  int32_t n[kMaxRagged];
 };
 
 // Rows [0, n0) of a slice are old rows, rows [n0, n) the pending frames of a
@@ -285,7 +302,7 @@ struct Whole {
 // pending one), which are not in the cache yet (ipv_stretch.hpp). Frame
 // f of the call has frame id id0 + f and patch ids patch0, patch0 + 1, ...
 struct Stretch {
-  static constexpr bool kNew = true;
+  static constexpr bool kNew = true, kRagged = false;
   const char* K;      // the call's frames, at the launch's first slice: frame f of slice s
   const char* V;      //   is `rows` contiguous rows at f * stride + s * rows * row bytes
   int64_t stride;
@@ -301,6 +318,35 @@ struct Stretch {
     return patch0 + (int32_t)(e - fast_div(e, rows) * rows.d);
   }
 };
+
+// Rows of a slice, of a launch made for n rows.
+template <class ST>
+__device__ __forceinline__ int32_t slice_rows(const ST& st, int32_t n, uint32_t slice) {
+  if constexpr (ST::kRagged) return st.n[fast_div(slice, st.per_stream)];
+  return n;
+}
+
+// The slice of tile-grid slice number i; past the last one for the padding.
+template <class ST>
+__device__ __forceinline__ uint32_t tile_slice(const ST& st, uint32_t i) {
+  if constexpr (ST::kRagged) {
+    const uint32_t a = fast_div(i, st.per_xcd);
+    return (i - a * st.per_xcd.d) * 8u + a;
+  }
+  return i;
+}
+
+// Tiles of a ragged launch that have no rows: slice past the last one, or
+// first row x0 past the slice's rows (n: its count).
+template <class ST>
+__device__ __forceinline__ bool no_tile(const ST& st, uint32_t slice, uint32_t& n, uint32_t x0) {
+  if constexpr (ST::kRagged) {
+    if (slice >= st.slices) return true;
+    n = (uint32_t)slice_rows(st, (int32_t)n, slice);
+    return x0 >= n;
+  }
+  return false;
+}
 
 // Row x's frame / patch id, given what the metadata array holds there.
 template <class ST>

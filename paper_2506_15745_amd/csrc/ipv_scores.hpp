@@ -152,32 +152,34 @@ __device__ __forceinline__ void table_block(const T* __restrict__ K, const int32
 // block of each slice also zeroes zero_per_slice words at
 // zero + slice * zero_per_slice (the compaction flags of a pass, saving a
 // launch). `slot`: GROUPS * r ints of LDS.
-template <typename T, int D>
+template <typename T, int D, class ST>
 __device__ __forceinline__ void table_grid_block(uint32_t tb, const T* __restrict__ K,
                                                  const int32_t* __restrict__ frame_idx,
                                                  const int32_t* __restrict__ patch_idx, int64_t S, int32_t n,
                                                  int32_t r, int32_t p, int32_t blocks_per_slice,
                                                  float* __restrict__ table, int32_t* __restrict__ first_recent,
                                                  uint32_t* err, uint32_t* __restrict__ zero, int32_t zero_per_slice,
-                                                 int32_t* slot) {
+                                                 int32_t* slot, const ST& st) {
   constexpr int GROUPS = 256 / (D / Lane<T>::EPL);
   const int64_t slice = tb / blocks_per_slice;
+  n = slice_rows(st, n, (uint32_t)slice);
+  if (ST::kRagged && n == 0) return;
   const int32_t q0 = (int32_t)(tb % blocks_per_slice) * GROUPS;
   if (zero && q0 == 0)
     for (int i = threadIdx.x; i < zero_per_slice; i += 256) zero[slice * zero_per_slice + i] = 0u;
   table_block<T, D, 256>(K, frame_idx, patch_idx, S, n, r, p, slice, q0, table, first_recent, err, slot);
 }
 
-template <typename T, int D>
+template <typename T, int D, class ST>
 __global__ __launch_bounds__(256) void k_recent_table(const T* __restrict__ K, const int32_t* __restrict__ frame_idx,
                                                       const int32_t* __restrict__ patch_idx, int64_t S, int32_t n,
                                                       int32_t r, int32_t p, int32_t blocks_per_slice,
                                                       float* __restrict__ table, int32_t* __restrict__ first_recent,
                                                       uint32_t* err, uint32_t* __restrict__ zero,
-                                                      int32_t zero_per_slice) {
+                                                      int32_t zero_per_slice, ST st) {
   extern __shared__ int32_t slot[];
   table_grid_block<T, D>(blockIdx.x, K, frame_idx, patch_idx, S, n, r, p, blocks_per_slice, table, first_recent, err,
-                         zero, zero_per_slice, slot);
+                         zero, zero_per_slice, slot, st);
 }
 
 // ---------------------------------------------------------------- TaR / VaN row sweep
@@ -362,28 +364,31 @@ __device__ __forceinline__ void sweep_tile(const T* __restrict__ K, const T* __r
 #define IPV_ARGS_NOW(...) asm volatile("" ::__VA_ARGS__)
 
 // grid: padded to a multiple of 8; work w = (slice * frame_blocks + frame block) * col_blocks + column block.
-// sure_past: rows below it are past whatever the frame ids say (n - r * p:
-// the window holds at most r frames of at most p rows), so a tile that ends
-// there does not wait for the slice's window start.
-template <typename T, int D, bool TAR, bool VAN>
+// window: r * p. Rows below n - window are past whatever the frame ids say (the
+// window holds at most r frames of at most p rows), so a tile that ends there
+// does not wait for the slice's window start.
+template <typename T, int D, bool TAR, bool VAN, class ST>
 __global__ __launch_bounds__(256) void k_score_sweep(const T* __restrict__ K, const T* __restrict__ V,
                                                      const int32_t* __restrict__ patch_idx, int64_t S, int32_t n,
                                                      int32_t p, const float* __restrict__ table,
                                                      const int32_t* __restrict__ first_recent,
                                                      float* __restrict__ tar, float* __restrict__ van,
-                                                     uint32_t* err, TileGrid g, int32_t sure_past) {
+                                                     uint32_t* err, TileGrid g, int32_t window, ST st) {
   using C = SweepCfg<T, D>;
   IPV_ARGS_NOW("s"(K), "s"(V), "s"(patch_idx), "s"(S), "s"(n), "s"(p), "s"(table), "s"(first_recent), "s"(tar),
-               "s"(van), "s"(g.col_blocks.m), "s"(g.frame_blocks.m), "s"(g.n_work), "s"(g.blocks), "s"(sure_past));
+               "s"(van), "s"(g.col_blocks.m), "s"(g.frame_blocks.m), "s"(g.n_work), "s"(g.blocks), "s"(window));
   const uint32_t logical = xcd_logical_id(blockIdx.x, g.blocks);
   if (logical >= g.n_work) return;
   const uint32_t tile = fast_div(logical, g.col_blocks);
   const uint32_t colblock = logical - tile * g.col_blocks.d;
-  const uint32_t slice = fast_div(tile, g.frame_blocks);
-  const uint32_t f0 = (tile - slice * g.frame_blocks.d) * C::U;
-  const bool tail = (int64_t)(f0 + C::U) * p > sure_past;
-  const uint32_t rec = TAR && tail ? (uint32_t)first_recent[slice] : (uint32_t)n;
-  sweep_tile<T, D, TAR, VAN>(K, V, patch_idx, S, n, p, table, rec, tar, van, err, slice, f0, colblock, threadIdx.x);
+  const uint32_t place = fast_div(tile, g.frame_blocks);
+  const uint32_t f0 = (tile - place * g.frame_blocks.d) * C::U;
+  const uint32_t slice = tile_slice(st, place);
+  uint32_t rows = (uint32_t)n;
+  if (no_tile(st, slice, rows, f0 * (uint32_t)p)) return;
+  const bool tail = (int64_t)(f0 + C::U) * p > (int64_t)rows - window;
+  const uint32_t rec = TAR && tail ? (uint32_t)first_recent[slice] : rows;
+  sweep_tile<T, D, TAR, VAN>(K, V, patch_idx, S, rows, p, table, rec, tar, van, err, slice, f0, colblock, threadIdx.x);
 }
 
 // The recent-key table and the VaN half of the sweep in one launch. The VaN
@@ -394,7 +399,7 @@ __global__ __launch_bounds__(256) void k_score_sweep(const T* __restrict__ K, co
 // table blocks leave and stream V meanwhile. The TaR half of the sweep reads
 // the table, so it is the next launch. table_padded is a multiple of 8, so
 // tile block i + table_padded runs on XCD i % 8.
-template <typename T, int D>
+template <typename T, int D, class ST>
 __global__ __launch_bounds__(256) void k_table_van(const T* __restrict__ K, const T* __restrict__ V,
                                                    const int32_t* __restrict__ frame_idx,
                                                    const int32_t* __restrict__ patch_idx, int64_t S, int32_t n,
@@ -402,12 +407,12 @@ __global__ __launch_bounds__(256) void k_table_van(const T* __restrict__ K, cons
                                                    uint32_t table_padded, uint32_t table_real,
                                                    float* __restrict__ table, int32_t* __restrict__ first_recent,
                                                    uint32_t* err, uint32_t* __restrict__ zero, int32_t zero_per_slice,
-                                                   float* __restrict__ van, TileGrid g) {
+                                                   float* __restrict__ van, TileGrid g, ST st) {
   extern __shared__ int32_t slot[];
   if (blockIdx.x < table_padded) {
     if (blockIdx.x < table_real)
       table_grid_block<T, D>(blockIdx.x, K, frame_idx, patch_idx, S, n, r, p, blocks_per_slice, table, first_recent,
-                             err, zero, zero_per_slice, slot);
+                             err, zero, zero_per_slice, slot, st);
     return;
   }
   using C = SweepCfg<T, D>;
@@ -417,9 +422,12 @@ __global__ __launch_bounds__(256) void k_table_van(const T* __restrict__ K, cons
   if (logical >= g.n_work) return;
   const uint32_t tile = fast_div(logical, g.col_blocks);
   const uint32_t colblock = logical - tile * g.col_blocks.d;
-  const uint32_t slice = fast_div(tile, g.frame_blocks);
-  const uint32_t f0 = (tile - slice * g.frame_blocks.d) * C::U;
-  sweep_tile<T, D, false, true>(K, V, patch_idx, S, n, p, table, n, nullptr, van, err, slice, f0, colblock,
+  const uint32_t place = fast_div(tile, g.frame_blocks);
+  const uint32_t f0 = (tile - place * g.frame_blocks.d) * C::U;
+  const uint32_t slice = tile_slice(st, place);
+  uint32_t rows = (uint32_t)n;
+  if (no_tile(st, slice, rows, f0 * (uint32_t)p)) return;
+  sweep_tile<T, D, false, true>(K, V, patch_idx, S, rows, p, table, rows, nullptr, van, err, slice, f0, colblock,
                                 threadIdx.x);
 }
 
@@ -500,10 +508,13 @@ __device__ __forceinline__ void pool_cv_block(const float* __restrict__ van, int
 }
 
 // One workgroup per (stream, layer).
+template <class ST>
 __global__ __launch_bounds__(kPoolThreads) void k_pool_cv(const float* __restrict__ van, int64_t S, int32_t n,
                                                           int32_t H, double tau1, double tau2, double tau3,
                                                           int32_t* __restrict__ pool_ws,
-                                                          int32_t* __restrict__ pool_out) {
+                                                          int32_t* __restrict__ pool_out, ST st) {
+  n = slice_rows(st, n, blockIdx.x * (uint32_t)H);
+  if (ST::kRagged && n == 0) return;
   __shared__ double red[kPoolThreads / kWave];
   pool_cv_block<kPoolThreads>(van, S, n, H, tau1, tau2, tau3, pool_ws, pool_out, blockIdx.x, threadIdx.x, red);
 }
@@ -576,6 +587,8 @@ __global__ __launch_bounds__(kPoolThreads) void k_pool_apply(float* __restrict__
   __shared__ int32_t slots;  // frame slots of the round that hold a row
   const int tid = threadIdx.x;
   const int64_t slice = blockIdx.x;
+  n = slice_rows(st, n, blockIdx.x);
+  if (ST::kRagged && n == 0) return;
   const int32_t k = pool_ws[slice / H];
   if (k != 3 && k != 5 && k != 7) return;  // 1: no pooling
   const int32_t p = grid_h * grid_w, FR = kPoolCells / p;
@@ -690,19 +703,21 @@ __global__ __launch_bounds__(kPoolThreads) void k_pool_apply(float* __restrict__
 // [0, cv_padded) compute the CV of (stream, layer) blockIdx.x (those at or
 // past cv_real return at once), the rest are TaR tiles as in k_score_sweep.
 // cv_padded is a multiple of 8, so tile block i + cv_padded runs on XCD i % 8.
-template <typename T, int D>
+template <typename T, int D, class ST>
 __global__ __launch_bounds__(256) void k_tar_sweep_cv(const T* __restrict__ K, const int32_t* __restrict__ patch_idx,
                                                       int64_t S, int32_t n, int32_t p, const float* __restrict__ table,
                                                       const int32_t* __restrict__ first_recent,
                                                       float* __restrict__ tar, uint32_t* err, TileGrid g,
-                                                      int32_t sure_past, const float* __restrict__ van, int32_t H,
+                                                      int32_t window, const float* __restrict__ van, int32_t H,
                                                       double tau1, double tau2, double tau3,
                                                       int32_t* __restrict__ pool_ws, uint32_t cv_padded,
-                                                      uint32_t cv_real) {
+                                                      uint32_t cv_real, ST st) {
   __shared__ double red[256 / kWave];
   if (blockIdx.x < cv_padded) {
-    if (blockIdx.x < cv_real)
-      pool_cv_block<256>(van, S, n, H, tau1, tau2, tau3, pool_ws, nullptr, blockIdx.x, threadIdx.x, red);
+    if (blockIdx.x >= cv_real) return;
+    n = slice_rows(st, n, blockIdx.x * (uint32_t)H);
+    if (ST::kRagged && n == 0) return;
+    pool_cv_block<256>(van, S, n, H, tau1, tau2, tau3, pool_ws, nullptr, blockIdx.x, threadIdx.x, red);
     return;
   }
   using C = SweepCfg<T, D>;
@@ -710,11 +725,14 @@ __global__ __launch_bounds__(256) void k_tar_sweep_cv(const T* __restrict__ K, c
   if (logical >= g.n_work) return;
   const uint32_t tile = fast_div(logical, g.col_blocks);
   const uint32_t colblock = logical - tile * g.col_blocks.d;
-  const uint32_t slice = fast_div(tile, g.frame_blocks);
-  const uint32_t f0 = (tile - slice * g.frame_blocks.d) * C::U;
-  const bool tail = (int64_t)(f0 + C::U) * p > sure_past;
-  const uint32_t rec = tail ? (uint32_t)first_recent[slice] : (uint32_t)n;
-  sweep_tile<T, D, true, false>(K, nullptr, patch_idx, S, n, p, table, rec, tar, nullptr, err, slice, f0, colblock,
+  const uint32_t place = fast_div(tile, g.frame_blocks);
+  const uint32_t f0 = (tile - place * g.frame_blocks.d) * C::U;
+  const uint32_t slice = tile_slice(st, place);
+  uint32_t rows = (uint32_t)n;
+  if (no_tile(st, slice, rows, f0 * (uint32_t)p)) return;
+  const bool tail = (int64_t)(f0 + C::U) * p > (int64_t)rows - window;
+  const uint32_t rec = tail ? (uint32_t)first_recent[slice] : rows;
+  sweep_tile<T, D, true, false>(K, nullptr, patch_idx, S, rows, p, table, rec, tar, nullptr, err, slice, f0, colblock,
                                 threadIdx.x);
 }
 

@@ -646,6 +646,8 @@ __global__ __launch_bounds__(NT) void k_select_uniform(const int32_t* __restrict
                                                        uint32_t* err, int32_t heads, uint32_t* __restrict__ zero,
                                                        int32_t zero_per_slice, ST st, EM em) {
   __shared__ SelShared<NT> sh;
+  n = slice_rows(st, n, blockIdx.x * (uint32_t)heads);
+  if (ST::kRagged && n == 0) return;
   uniform_slice<NT, RPT, VEC>(frame_idx, S, n, budget, r, keep_idx, err, (int64_t)blockIdx.x * heads, heads, zero,
                               zero_per_slice, sh, st, em);
 }
@@ -658,6 +660,8 @@ __global__ __launch_bounds__(NT) void k_select(const float* __restrict__ tar, co
                                                int32_t* __restrict__ keep_idx, uint32_t* err, int32_t heads,
                                                uint32_t tflip, uint32_t vflip, ST st, EM em) {
   __shared__ SelShared<NT> sh;
+  n = slice_rows(st, n, blockIdx.x * (uint32_t)heads);
+  if (ST::kRagged && n == 0) return;
   select_slice<NT, RPT, VEC>(tar, van, frame_idx, S, n, budget, tar_total, r, keep_idx, err,
                              (int64_t)blockIdx.x * heads, heads, tflip, vflip, sh, st, em);
 }
