@@ -344,6 +344,11 @@ ipv_status select(const Dims& d, const float* tar, const float* van, const int32
   // longer (16-stream 7B-class batch: 65 against 93 us).
   const int64_t groups = d.slices / ((mode & IPV_HEAD_SHARED) ? d.H : 1);
   const bool many = groups > kComputeUnits && rpt <= 8;
+  // Beyond 32 rows a thread the 128 registers of a 1024-thread block bound it:
+  // 64 rows a thread, with both columns loaded together, spilled (640 slices of
+  // 32928 rows 391 us, against 142 us for 32768 rows at 32 a thread). With the
+  // columns one after the other and 36 rows a thread 150 us; 48 for up to 49152
+  // rows 278 us (499 before), 64 beyond 393 us (661 before, 65536 rows).
 #define IPV_UNIFORM(RPT) return run_uniform<RPT>(d, fr, n, budget, r, keep, err, st, mode, zero, zero_per_slice, rows, em)
 #define IPV_SELECT(RPT) return run_select<RPT>(d, tar, van, fr, n, budget, tar_total, r, keep, err, st, mode, rows, em)
   if (mode & IPV_UNIFORM_SELECT) {
@@ -360,6 +365,8 @@ ipv_status select(const Dims& d, const float* tar, const float* van, const int32
   if (rpt <= 12) IPV_SELECT(12);
   if (rpt <= 16) IPV_SELECT(16);
   if (rpt <= 32) IPV_SELECT(32);
+  if (rpt <= 36) IPV_SELECT(36);
+  if (rpt <= 48) IPV_SELECT(48);
   IPV_SELECT(64);
 #undef IPV_UNIFORM
 #undef IPV_SELECT

@@ -228,6 +228,10 @@ __device__ __forceinline__ void load_row_run(const void* __restrict__ col, int64
 template <int RPT>
 constexpr int head_batch() { return RPT <= 8 ? 3 : 1; }
 
+// ... and how many rows of them at a time (registers).
+template <int RPT>
+constexpr int head_run() { return RPT <= 32 ? RPT : 4; }
+
 // A score run summed over `heads` consecutive slices (column stride S) in
 // fp32, head 0 first, starting from +0 (the order the keep decision is
 // defined in); heads == 1 is the slice's own run. Absent heads of a batch
@@ -235,20 +239,25 @@ constexpr int head_batch() { return RPT <= 8 ? 3 : 1; }
 template <int RPT, bool VEC>
 __device__ __forceinline__ void load_score_run(const float* __restrict__ col, int64_t S, int32_t heads, int64_t row0,
                                                uint32_t (&out)[RPT]) {
-  constexpr int G = head_batch<RPT>();
+  constexpr int G = head_batch<RPT>(), R = head_run<RPT>();
   load_row_run<RPT, VEC>(col, S, row0, out);
   if (heads == 1) return;
 #pragma unroll
   for (int i = 0; i < RPT; ++i) out[i] = __float_as_uint(0.f + __uint_as_float(out[i]));
 #pragma unroll 1
   for (int32_t h = 1; h < heads; h += G) {
-    uint32_t t[G][RPT];
 #pragma unroll
-    for (int g = 0; g < G; ++g) load_row_run<RPT, VEC>(col + min(h + g, heads - 1) * S, S, row0, t[g], h + g < heads);
+    for (int i0 = 0; i0 < RPT; i0 += R) {
+      uint32_t t[G][R];
 #pragma unroll
-    for (int g = 0; g < G; ++g)
+      for (int g = 0; g < G; ++g)
+        load_row_run<R, VEC>(col + min(h + g, heads - 1) * S, S, row0 + i0, t[g], h + g < heads);
 #pragma unroll
-      for (int i = 0; i < RPT; ++i) out[i] = __float_as_uint(__uint_as_float(out[i]) + __uint_as_float(t[g][i]));
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+          out[i0 + i] = __float_as_uint(__uint_as_float(out[i0 + i]) + __uint_as_float(t[g][i]));
+    }
   }
 }
 
@@ -257,17 +266,21 @@ __device__ __forceinline__ void load_score_run(const float* __restrict__ col, in
 template <int RPT, bool VEC>
 __device__ __forceinline__ bool heads_differ(const int32_t* __restrict__ fr0, int64_t S, int32_t heads, int64_t row0,
                                              int32_t n, const uint32_t (&fr)[RPT]) {
-  constexpr int G = head_batch<RPT>();
+  constexpr int G = head_batch<RPT>(), R = head_run<RPT>();
   bool diff = false;
 #pragma unroll 1
   for (int32_t h = 1; h < heads; h += G) {
-    uint32_t t[G][RPT];
 #pragma unroll
-    for (int g = 0; g < G; ++g) load_row_run<RPT, VEC>(fr0 + min(h + g, heads - 1) * S, S, row0, t[g], h + g < heads);
+    for (int i0 = 0; i0 < RPT; i0 += R) {
+      uint32_t t[G][R];
 #pragma unroll
-    for (int g = 0; g < G; ++g)
+      for (int g = 0; g < G; ++g)
+        load_row_run<R, VEC>(fr0 + min(h + g, heads - 1) * S, S, row0 + i0, t[g], h + g < heads);
 #pragma unroll
-      for (int i = 0; i < RPT; ++i) diff |= h + g < heads && row0 + i < n && t[g][i] != fr[i];
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int i = 0; i < R; ++i) diff |= h + g < heads && row0 + i0 + i < n && t[g][i] != fr[i0 + i];
+    }
   }
   return diff;
 }
@@ -400,11 +413,12 @@ __device__ __forceinline__ void select_slice(const float* __restrict__ tar, cons
   };
 
   // all loads are issued up front; with many rows per thread the VaN column
-  // waits until the TaR stage is done, to stay within the register budget
-  constexpr bool kEarlyVan = RPT <= 16;
+  // waits until the TaR stage is done, to stay within the register budget,
+  // and beyond 32 the TaR column waits for the frame ids to be turned into masks
+  constexpr bool kEarlyVan = RPT <= 16, kEarlyTar = RPT <= 32;
   uint32_t fr[RPT], kt[RPT], kv[RPT];
   load_row_run<RPT, VEC>(frame_idx + base, S, row0, fr);
-  load_score_run<RPT, VEC>(tar + base, S, heads, row0, kt);
+  if (kEarlyTar) load_score_run<RPT, VEC>(tar + base, S, heads, row0, kt);
   if (kEarlyVan) load_score_run<RPT, VEC>(van + base, S, heads, row0, kv);
   const __amdgpu_buffer_rsrc_t frs = buffer_rsrc(frame_idx + base, (uint32_t)(S * 4));
   const int32_t last = row_frame(st, n - 1, (int32_t)__builtin_amdgcn_raw_buffer_load_b32(frs, (uint32_t)(n - 1) * 4u, 0, 0));
@@ -436,13 +450,21 @@ __device__ __forceinline__ void select_slice(const float* __restrict__ tar, cons
       if (rec && (int64_t)prev < thr) sh.first_recent = (int32_t)(row0 + i);
       bad |= f < prev;
       prev = f;
-      nan_t |= !rec && __uint_as_float(kt[i]) != __uint_as_float(kt[i]);
+      if (kEarlyTar) nan_t |= !rec && __uint_as_float(kt[i]) != __uint_as_float(kt[i]);
       if (kEarlyVan) nan_v |= !rec && __uint_as_float(kv[i]) != __uint_as_float(kv[i]);
     }
-    kt[i] = order_key(__uint_as_float(kt[i])) ^ tflip;
+    if (kEarlyTar) kt[i] = order_key(__uint_as_float(kt[i])) ^ tflip;
     if (kEarlyVan) kv[i] = order_key(__uint_as_float(kv[i])) ^ vflip;
   }
   const uint64_t past = valid & ~recent;
+  if (!kEarlyTar) {
+    load_score_run<RPT, VEC>(tar + base, S, heads, row0, kt);
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      nan_t |= ((past >> i) & 1ull) && __uint_as_float(kt[i]) != __uint_as_float(kt[i]);
+      kt[i] = order_key(__uint_as_float(kt[i])) ^ tflip;
+    }
+  }
   // key ranges of both stages over the past rows, and the frame check
   uint32_t tmn = 0xffffffffu, tmx = 0u, vmn = 0xffffffffu, vmx = 0u;
 #pragma unroll
