@@ -17,6 +17,7 @@ Tensor layouts (all contiguous, on the same GPU):
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 import torch
@@ -122,9 +123,17 @@ def shape_of(K: torch.Tensor, grid_h: int, grid_w: int) -> Shape:
     return Shape(B, L, H, D, S, grid_h, grid_w, _dtype_code(K))
 
 
+@functools.lru_cache(maxsize=256)
+def _shape(B, L, H, D, S, grid_h, grid_w, dtype) -> Shape:
+    """A Shape for the library to read (shared: never handed to a caller)."""
+    return Shape(B, L, H, D, S, grid_h, grid_w, dtype)
+
+
 def _ptr(t):
     if t is None:
         return None
+    if t.is_cuda and t.is_contiguous():
+        return t.data_ptr()
     if t.device.type != "cuda":
         raise IpvError(ERR_ARG, "tensors must be in GPU memory (got %s)" % t.device)
     if not t.is_contiguous():
@@ -140,6 +149,8 @@ def _expect(what, t, shape, dtype, device, optional=False):
         if optional:
             return
         raise IpvError(ERR_NULL, "%s is required" % what)
+    if t.dtype is dtype and t.shape == shape and t.device == device:
+        return
     if t.dtype != dtype:
         raise IpvError(ERR_DTYPE, "%s must be %s (got %s)" % (what, dtype, t.dtype))
     if tuple(t.shape) != tuple(shape):
@@ -197,6 +208,44 @@ def _check_pass_buffers(K, V, frame_idx, patch_idx, tar, van, keep_idx, budget, 
         _check_ws(ws, K.device, optional)
 
 
+# A call's host time is its checks: 21 us for ipv_ckv_step when every tensor's
+# shape, dtype and device went through _expect and the pointers through _ptr, 12.6 us
+# with the whole set read once here. (A frame's append takes 8 us on the GPU.)
+def _pass_ptrs(K, V, frame_idx, patch_idx, tar, van, keep_idx, budget, ws, grid_h, grid_w):
+    """(shape, device, K, V, frame_idx, patch_idx, tar, van, keep_idx, ws) as
+    the library takes them, or None when a check fails or a buffer is missing:
+    the checks one by one then say whether that is an error and which."""
+    if tar is None or van is None or keep_idx is None or ws is None:
+        return None
+    kd, dev, kv = K.dtype, K.get_device(), K.shape
+    code = BF16 if kd is torch.bfloat16 else F32 if kd is torch.float32 else -1
+    if code < 0 or dev < 0 or len(kv) != 5:
+        return None
+    B, L, H, S, D = kv
+    rows, i32, f32 = (B, L, H, S), torch.int32, torch.float32
+    if (V.dtype is kd and frame_idx.dtype is i32 and patch_idx.dtype is i32 and tar.dtype is f32 and van.dtype is f32
+            and keep_idx.dtype is i32 and V.shape == kv and frame_idx.shape == rows and patch_idx.shape == rows
+            and tar.shape == rows and van.shape == rows and keep_idx.shape == (B, L, H, int(budget))
+            and V.get_device() == dev and frame_idx.get_device() == dev and patch_idx.get_device() == dev
+            and tar.get_device() == dev and van.get_device() == dev and keep_idx.get_device() == dev
+            and ws.get_device() == dev and K.is_cuda and K.is_contiguous() and V.is_contiguous()
+            and frame_idx.is_contiguous() and patch_idx.is_contiguous() and tar.is_contiguous()
+            and van.is_contiguous() and keep_idx.is_contiguous() and ws.is_contiguous()):
+        return (_shape(B, L, H, D, S, grid_h, grid_w, code), dev, K.data_ptr(), V.data_ptr(), frame_idx.data_ptr(),
+                patch_idx.data_ptr(), tar.data_ptr(), van.data_ptr(), keep_idx.data_ptr(), ws.data_ptr())
+    return None
+
+
+def _checked_ptrs(K, V, frame_idx, patch_idx, tar, van, keep_idx, budget, ws, grid_h, grid_w, mode, optional=False):
+    """(shape, K, V, frame_idx, patch_idx, tar, van, keep_idx, ws), every check made."""
+    got = _pass_ptrs(K, V, frame_idx, patch_idx, tar, van, keep_idx, budget, ws, grid_h, grid_w)
+    if got is not None:
+        return got[:1] + got[2:]
+    s = shape_of(K, grid_h, grid_w)
+    _check_pass_buffers(K, V, frame_idx, patch_idx, tar, van, keep_idx, budget, ws, optional=optional, mode=mode)
+    return (s, _ptr(K), _ptr(V), _ptr(frame_idx), _ptr(patch_idx), _ptr(tar), _ptr(van), _ptr(keep_idx), _ptr(ws))
+
+
 def _check_new_rows(K, K_new, V_new):
     """K_new / V_new: [B, L, H, rows, D] with the cache's dtype."""
     if K_new.dtype != K.dtype or V_new.dtype != K.dtype:
@@ -219,6 +268,8 @@ def counts(n_tokens, streams: int):
 
 def _stream(stream):
     if stream is None:
+        if torch.cuda.is_initialized():  # the handle of torch.cuda.current_stream(), without the object
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream
 
@@ -288,14 +339,12 @@ def ipv_compact(K, V, frame_idx, patch_idx, n_tokens, keep_idx, budget, ws, grid
 
 def ipv_compress(K, V, frame_idx, patch_idx, n_tokens, budget, alpha, recent_frames, cv_tau, tar, van, keep_idx,
                  ws, grid_h, grid_w, stream=None, mode=0):
-    s = shape_of(K, grid_h, grid_w)
-    _check_pass_buffers(K, V, frame_idx, patch_idx, tar, van, keep_idx, budget, ws, mode=mode)
+    s, k, v, fr, pa, tr, vn, keep, w = _checked_ptrs(K, V, frame_idx, patch_idx, tar, van, keep_idx, budget, ws, grid_h,
+                                                     grid_w, mode)
     tau = None if cv_tau is None else (ctypes.c_double * 3)(*cv_tau)
-    _check(lib().ipv_compress(ctypes.byref(s), _ptr(K), _ptr(V), _ptr(frame_idx), _ptr(patch_idx),
-                              counts(n_tokens, s.streams),
-                              budget, float(alpha), recent_frames, mode, None if tau is None else ctypes.addressof(tau),
-                              _ptr(tar), _ptr(van), _ptr(keep_idx), _ptr(ws), _ws_bytes(ws), _stream(stream)),
-           "ipv_compress")
+    _check(lib().ipv_compress(ctypes.byref(s), k, v, fr, pa, counts(n_tokens, s.streams), budget, float(alpha),
+                              recent_frames, mode, None if tau is None else ctypes.addressof(tau), tr, vn, keep, w,
+                              _ws_bytes(ws), _stream(stream)), "ipv_compress")
 
 
 def ipv_compress_timed(K, V, frame_idx, patch_idx, n_tokens, budget, alpha, recent_frames, cv_tau, tar, van,
@@ -349,19 +398,28 @@ def ipv_ckv_step(K, V, frame_idx, patch_idx, n_tokens, K_new, V_new, frame_id, f
     """Append, then compress to `budget` every stream that holds >= mem_cap
     rows. Returns (row counts, whether each stream's pass ran): ints for an
     int n_tokens (every stream then behaves alike), else lists."""
-    s = shape_of(K, grid_h, grid_w)
-    _check_cache(K, V, frame_idx, patch_idx)
-    _check_new_rows(K, K_new, V_new)
-    _check_pass_buffers(K, V, frame_idx, patch_idx, tar, van, keep_idx, budget, ws, optional=True, mode=mode)
+    got = _pass_ptrs(K, V, frame_idx, patch_idx, tar, van, keep_idx, budget, ws, grid_h, grid_w)
+    new = K_new.shape
+    if (got is not None and len(new) == 5 and V_new.shape == new and K_new.dtype is K.dtype and V_new.dtype is K.dtype
+            and (new[0], new[1], new[2], new[4]) == (got[0].streams, got[0].layers, got[0].kv_heads, got[0].head_dim)
+            and K_new.get_device() == got[1] and V_new.get_device() == got[1] and K_new.is_contiguous()
+            and V_new.is_contiguous()):
+        s, _, k, v, fr, pa, tr, vn, keep, w = got
+        kn, vnew = K_new.data_ptr(), V_new.data_ptr()
+    else:
+        s = shape_of(K, grid_h, grid_w)
+        _check_cache(K, V, frame_idx, patch_idx)
+        _check_new_rows(K, K_new, V_new)
+        s, k, v, fr, pa, tr, vn, keep, w = _checked_ptrs(K, V, frame_idx, patch_idx, tar, van, keep_idx, budget, ws,
+                                                         grid_h, grid_w, mode, optional=True)
+        kn, vnew = _ptr(K_new), _ptr(V_new)
     tau = None if cv_tau is None else (ctypes.c_double * 3)(*cv_tau)
-    n_out, comp = (ctypes.c_int32 * s.streams)(), (ctypes.c_int32 * s.streams)()
-    _check(lib().ipv_ckv_step(ctypes.byref(s), _ptr(K), _ptr(V), _ptr(frame_idx), _ptr(patch_idx),
-                              counts(n_tokens, s.streams),
-                              _ptr(K_new), _ptr(V_new), K_new.shape[3], frame_id, first_patch, mem_cap, budget,
-                              float(alpha), recent_frames, mode, None if tau is None else ctypes.addressof(tau),
-                              _ptr(tar),
-                              _ptr(van), _ptr(keep_idx), _ptr(ws), _ws_bytes(ws),
-                              n_out, comp, _stream(stream)), "ipv_ckv_step")
+    out = (ctypes.c_int32 * s.streams)
+    n_out, comp = out(), out()
+    _check(lib().ipv_ckv_step(ctypes.byref(s), k, v, fr, pa, counts(n_tokens, s.streams), kn, vnew, new[3], frame_id,
+                              first_patch, mem_cap, budget, float(alpha), recent_frames, mode,
+                              None if tau is None else ctypes.addressof(tau), tr, vn, keep, w, _ws_bytes(ws), n_out,
+                              comp, _stream(stream)), "ipv_ckv_step")
     if isinstance(n_tokens, int):
         return n_out[0], bool(comp[0])
     return list(n_out), [bool(c) for c in comp]
@@ -379,15 +437,15 @@ def ipv_ckv_stream(K, V, frame_idx, patch_idx, n_tokens, frames_K, frames_V, fir
     if frames_K.shape != frames_V.shape or frames_K.dim() != 6 or frames_K.shape[1:4] != K.shape[:3] \
             or frames_K.shape[5] != K.shape[4]:
         raise IpvError(ERR_SHAPE, "frames_K/V must be [F, B, L, H, rows, D] like the cache")
-    _check_pass_buffers(K, V, frame_idx, patch_idx, tar, van, keep_idx, budget, ws, optional=True, mode=mode)
+    s, k, v, fr, pa, tr, vn, keep, w = _checked_ptrs(K, V, frame_idx, patch_idx, tar, van, keep_idx, budget, ws, grid_h,
+                                                     grid_w, mode, optional=True)
     tau = None if cv_tau is None else (ctypes.c_double * 3)(*cv_tau)
     ns = counts(n_tokens, s.streams)
     passes = (ctypes.c_int32 * s.streams)()
-    _check(lib().ipv_ckv_stream(ctypes.byref(s), _ptr(K), _ptr(V), _ptr(frame_idx), _ptr(patch_idx), ns,
-                                _ptr(frames_K), _ptr(frames_V), frames_K.shape[0], frames_K.shape[4], first_frame_id,
-                                mem_cap, budget, float(alpha), recent_frames, mode,
-                                None if tau is None else ctypes.addressof(tau), _ptr(tar), _ptr(van), _ptr(keep_idx),
-                                _ptr(ws), _ws_bytes(ws), passes, _stream(stream)), "ipv_ckv_stream")
+    _check(lib().ipv_ckv_stream(ctypes.byref(s), k, v, fr, pa, ns, _ptr(frames_K), _ptr(frames_V), frames_K.shape[0],
+                                frames_K.shape[4], first_frame_id, mem_cap, budget, float(alpha), recent_frames, mode,
+                                None if tau is None else ctypes.addressof(tau), tr, vn, keep, w, _ws_bytes(ws), passes,
+                                _stream(stream)), "ipv_ckv_stream")
     if isinstance(n_tokens, int):
         return ns[0], passes[0]
     return list(ns), list(passes)
