@@ -13,6 +13,7 @@
 #include "ipv_compact.hpp"
 #include "ipv_scores.hpp"
 #include "ipv_select.hpp"
+#include "ipv_small.hpp"
 #include "ipv_stretch.hpp"
 
 using namespace ipv;
@@ -493,6 +494,82 @@ ipv_status stretch_gather(const Dims& d, void* K, void* V, const Stretch& sr, co
   return IPV_ERR_SHAPE;
 }
 
+// ------------------------------------------------------------ small slices (ipv_small.hpp)
+// Whether a pass over slices of at most n rows goes out as one launch, a
+// workgroup per slice: the plain scores (pooling and the other modes couple a
+// layer's slices or have steps of their own), slices that run all at once, and
+// 256 rows and 64 KB of keys at most. Passes as GPU time alone, four launches
+// against one (a graph of ten): 128 rows of 256 bytes 15.3 -> 13.3 us (2 slices),
+// 23.9 -> 16.3 (256 slices); 256 rows 18.4 -> 16.4, 32.6 -> 22.2. Beyond, the one
+// workgroup's share of the bandwidth counts: 512 rows of 256 bytes 17.8 -> 20.1,
+// of 64 bytes 16.5 -> 19.0, 512 slices of 64 bytes 42.8 -> 45.2. A caller that is
+// bound by its launches gains more (two passes and a gather of 128 rows: 7
+// launches -> 2, 38 -> 28 us a call).
+constexpr int64_t kSmallBytes = 64 << 10;
+bool small_pass(const Dims& d, int32_t n, int32_t r, uint32_t mode, const double* cv_tau) {
+  return !cv_tau && (mode & ~(uint32_t)(IPV_TAR_REVERSE | IPV_VAN_REVERSE)) == 0 && n <= kSmallRows && r <= 32 &&
+         d.slices <= kComputeUnits && (int64_t)n * d.D * d.elem <= kSmallBytes;
+}
+
+uint32_t flip_bits(uint32_t mode, uint32_t bit) { return (mode & bit) ? 0xffffffffu : 0u; }
+
+template <typename T, int D, class ST>
+ipv_status small_pass_t(const Dims& d, void* K, void* V, int32_t* fr, int32_t* pa, int32_t n, const ST& rows,
+                        int32_t budget, int32_t tar_total, int32_t r, uint32_t mode, float* tar, float* van,
+                        int32_t* keep, void* ws, hipStream_t st) {
+  constexpr int TG = kSmallThreads / (D / Lane<T>::EPL);
+  k_small_pass<T, D><<<dim3((uint32_t)d.slices), dim3(kSmallThreads), (size_t)TG * r * sizeof(int32_t), st>>>(
+      static_cast<char*>(K), static_cast<char*>(V), fr, pa, d.S, n, r, (int32_t)d.p, budget, tar_total, ws_table(ws),
+      ws_first(ws, d), tar, van, keep, err_word(ws), flip_bits(mode, IPV_TAR_REVERSE), flip_bits(mode, IPV_VAN_REVERSE),
+      rows);
+  return launched();
+}
+
+template <typename T, int D>
+ipv_status small_stretch_t(const Dims& d, void* K, void* V, const Stretch& sr, int32_t* fr, int32_t* pa, int32_t n,
+                           int32_t budget, int32_t tar_total, int32_t r, uint32_t mode, float* tar, float* van,
+                           uint32_t v0, const Emit& em, bool gather, void* ws, hipStream_t st) {
+  constexpr int TG = kSmallThreads / (D / Lane<T>::EPL);
+  k_small_stretch<T, D><<<dim3((uint32_t)d.slices), dim3(kSmallThreads), (size_t)TG * r * sizeof(int32_t), st>>>(
+      static_cast<char*>(K), static_cast<char*>(V), sr, fr, pa, d.S, n, r, (int32_t)d.p, budget, tar_total, ws_table(ws),
+      ws_first(ws, d), tar, van, v0, err_word(ws), flip_bits(mode, IPV_TAR_REVERSE), flip_bits(mode, IPV_VAN_REVERSE), em,
+      gather);
+  return launched();
+}
+
+// fn(T, D) for the shape's element type and head size
+#define IPV_BY_TYPE(d, CALL)                                                          \
+  if ((d).dtype == IPV_BF16) {                                                        \
+    if ((d).D == 32) CALL(uint16_t, 32);                                              \
+    if ((d).D == 64) CALL(uint16_t, 64);                                              \
+    if ((d).D == 128) CALL(uint16_t, 128);                                            \
+    if ((d).D == 256) CALL(uint16_t, 256);                                            \
+  } else {                                                                            \
+    if ((d).D == 32) CALL(float, 32);                                                 \
+    if ((d).D == 64) CALL(float, 64);                                                 \
+    if ((d).D == 128) CALL(float, 128);                                               \
+    if ((d).D == 256) CALL(float, 256);                                               \
+  }                                                                                   \
+  return IPV_ERR_SHAPE
+
+template <class ST>
+ipv_status run_small(const Dims& d, void* K, void* V, int32_t* fr, int32_t* pa, int32_t n, const ST& rows, int32_t budget,
+                     int32_t tar_total, int32_t r, uint32_t mode, float* tar, float* van, int32_t* keep, void* ws,
+                     hipStream_t st) {
+#define IPV_SMALL(T, DD) return small_pass_t<T, DD>(d, K, V, fr, pa, n, rows, budget, tar_total, r, mode, tar, van, keep, ws, st)
+  IPV_BY_TYPE(d, IPV_SMALL);
+#undef IPV_SMALL
+}
+
+ipv_status run_small_stretch(const Dims& d, void* K, void* V, const Stretch& sr, int32_t* fr, int32_t* pa, int32_t n,
+                             int32_t budget, int32_t tar_total, int32_t r, uint32_t mode, float* tar, float* van,
+                             uint32_t v0, const Emit& em, bool gather, void* ws, hipStream_t st) {
+#define IPV_SMALL(T, DD) \
+  return small_stretch_t<T, DD>(d, K, V, sr, fr, pa, n, budget, tar_total, r, mode, tar, van, v0, em, gather, ws, st)
+  IPV_BY_TYPE(d, IPV_SMALL);
+#undef IPV_SMALL
+}
+
 // ------------------------------------------------------------ append
 // `frames` consecutive frames of `rows` rows each into rows
 // [n, n + frames * rows) of every slice. Block row blockIdx.y takes slices
@@ -633,6 +710,8 @@ ipv_status compress_run(const Dims& d, void* K, void* V, int32_t* fr, int32_t* p
   const bool adjacent = (mode & IPV_TAR_ADJACENT) != 0;
   // with the recent-key table, the pooling CV runs in the TaR launch
   const bool cv_fused = cv_tau && !uniform && !adjacent;
+  if (!events && small_pass(d, n, r, mode, cv_tau))
+    return run_small(d, K, V, fr, pa, n, rows, budget, floor_share(alpha, budget), r, mode, tar, van, keep, ws, st);
   IPV_TRY(mark(0));
   if (uniform)
     IPV_TRY(mark(1));
@@ -905,7 +984,8 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
         sr.eoff = (uint32_t)l.pending * (uint32_t)rows - (uint32_t)l.n0;
         sr.id0 = first_frame_id;
         int32_t* places = reinterpret_cast<int32_t*>(ws_table(ws));
-        if (!uniform)
+        const bool small = small_pass(s, n, r, mode, cv_tau);
+        if (!uniform && !small)
           IPV_TRY(stretch_scores(s, k, v, sr, fr, pa, n, r, tr, vn, ws, st, chunks, adjacent,
                                  pool && !adjacent ? cv_tau : nullptr, l.passes > 0 && !pool));
         if (pool) IPV_TRY(pool_d(s, cv_tau, vn, fr, pa, n, sr, nullptr, ws, st, !adjacent));
@@ -915,10 +995,14 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
                       last ? s.S : budget,
                       last || pool || uniform ? nullptr : vn,
                       last ? keep : nullptr};
-        IPV_TRY(select(s, tr, vn, fr, n, sr, budget, floor_share(alpha, budget), r, keep, err_word(ws), st, mode,
+        if (small)
+          IPV_TRY(run_small_stretch(s, k, v, sr, fr, pa, n, budget, floor_share(alpha, budget), r, mode, tr, vn,
+                                    l.passes > 0 ? sr.n0 : 0u, em, last, ws, st));
+        else
+          IPV_TRY(select(s, tr, vn, fr, n, sr, budget, floor_share(alpha, budget), r, keep, err_word(ws), st, mode,
                        uniform && last ? ws_flags(ws, s) : nullptr, (int32_t)(compact_parts(s) * walk_words(chunks)),
                        em));
-        if (last) IPV_TRY(stretch_gather(s, k, v, sr, places, entry[b0].n0, budget, ws, st));
+        if (last && !small) IPV_TRY(stretch_gather(s, k, v, sr, places, entry[b0].n0, budget, ws, st));
         for (int64_t b = b0; b < e; ++b) {
           ls[b] = {budget, (int32_t)f + 1, l.passes + 1, l.total};
           ++passes[b];
