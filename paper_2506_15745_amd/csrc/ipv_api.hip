@@ -3,6 +3,7 @@
 // first launch, so a rejected call enqueues nothing and touches no buffer.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <mutex>
@@ -10,6 +11,7 @@
 
 #include "../../include/ipv.h"
 #include "ipv_adjacent.hpp"
+#include "ipv_ahead.hpp"
 #include "ipv_compact.hpp"
 #include "ipv_scores.hpp"
 #include "ipv_select.hpp"
@@ -286,6 +288,7 @@ __global__ void k_fill_i32(int32_t* p, int64_t count, int32_t v) {
 
 constexpr int kSelThreads = 1024;  // most threads of a selection workgroup
 constexpr int64_t kComputeUnits = 256;  // MI355X
+constexpr int64_t kAheadGroups = kComputeUnits * 3 / 4;
 
 // Threads of a selection workgroup: whole waves for the n rows at RPT rows a
 // thread, at most kSelThreads (the caller picks RPT >= n / kSelThreads).
@@ -294,6 +297,8 @@ uint32_t sel_threads(int32_t n, int RPT) {
   return (uint32_t)std::min(kSelThreads, (t + 63) / 64 * 64);
 }
 
+uint32_t flip_bits(uint32_t mode, uint32_t bit) { return (mode & bit) ? 0xffffffffu : 0u; }
+
 // mode: the reverse bits complement a stage's keys; IPV_HEAD_SHARED gives one
 // block (and one keep set) to each (stream, layer)
 template <int RPT, class ST, class EM>
@@ -301,8 +306,8 @@ ipv_status run_select(const Dims& d, const float* tar, const float* van, const i
                       int32_t tar_total, int32_t r, int32_t* keep, uint32_t* err, hipStream_t st, uint32_t mode,
                       const ST& rows, const EM& em) {
   const int32_t heads = (mode & IPV_HEAD_SHARED) ? (int32_t)d.H : 1;
-  const uint32_t tflip = (mode & IPV_TAR_REVERSE) ? 0xffffffffu : 0u;
-  const uint32_t vflip = (mode & IPV_VAN_REVERSE) ? 0xffffffffu : 0u;
+  const uint32_t tflip = flip_bits(mode, IPV_TAR_REVERSE);
+  const uint32_t vflip = flip_bits(mode, IPV_VAN_REVERSE);
   const dim3 grid((uint32_t)(d.slices / heads)), block(sel_threads(n, RPT));
   // 16-byte row-run loads need every slice to start 16-byte aligned
   if (d.S % 4 == 0)
@@ -410,56 +415,126 @@ ipv_status compact(const Dims& d, void* K, void* V, int32_t* fr, int32_t* pa, in
 // Scores of one pass over a run of slices. norms_known: van holds the old
 // rows' norms already. cv_tau: the TaR launch also computes the pooling CV.
 // zero_chunks > 0: the first kernel zeroes the flags of a gather that follows.
+// ahead: what the launch before has done already.
+struct AheadDone {
+  bool norms = false, table = false;
+};
+
 template <typename T, int D>
 ipv_status stretch_scores_t(const Dims& d, const char* K, const char* V, const Stretch& sr, const int32_t* fr,
-                            const int32_t* pa, int32_t n, int32_t r, float* tar, float* van, void* ws, hipStream_t st,
-                            int64_t zero_chunks, bool adjacent, const double* cv_tau, bool norms_known) {
+                            int32_t* pa, int32_t n, int32_t r, float* tar, float* van, void* ws, hipStream_t st,
+                            int64_t zero_chunks, bool adjacent, const double* cv_tau, bool norms_known, AheadDone ahead) {
   using C = SweepCfg<T, D>;
   constexpr uint32_t TILE = C::GROUPS * C::U;
   uint32_t* zero = zero_chunks > 0 ? ws_flags(ws, d) : nullptr;
   const int32_t zero_per_slice = (int32_t)(compact_parts(d) * walk_words(zero_chunks));
   const uint32_t slices = (uint32_t)d.slices;
-  const uint32_t v0 = norms_known ? sr.n0 : 0u;
+  const uint32_t v0 = ahead.norms ? (uint32_t)n : norms_known ? sr.n0 : 0u;
   const uint32_t van_tiles = ((uint32_t)n - v0 + TILE - 1) / TILE, van_work = slices * van_tiles;
+  const FastDiv van_div = make_fastdiv(std::max(1u, van_tiles));
+  int32_t* waiting = ahead.norms ? pa : nullptr;
   int32_t* first = ws_first(ws, d);
   if (adjacent) {
     const uint32_t walks = pad8(slices), quads = pad8((van_work + 3) / 4);
     k_stretch_prev_van<T, D><<<dim3(walks + quads), dim3(kPrevThreads), 0, st>>>(
         V, sr, fr, pa, d.S, n, r, (int32_t)d.p, ws_prev(ws), first, err_word(ws), zero, zero_per_slice, walks, slices,
-        van, v0, make_fastdiv(van_tiles), van_work, quads);
+        van, v0, van_div, van_work, quads);
     const uint32_t tiles = ((uint32_t)n + TILE - 1) / TILE, work = slices * tiles;
     k_stretch_adjacent<T, D><<<dim3(pad8(work)), dim3(256), 0, st>>>(K, sr, ws_prev(ws), d.S, n, first, tar,
-                                                                     make_fastdiv(tiles), work, pad8(work));
+                                                                     waiting, van, make_fastdiv(tiles), work, pad8(work));
     return launched();
   }
   const uint32_t blocks = (uint32_t)((d.p + C::GROUPS - 1) / C::GROUPS), table = slices * blocks;
-  k_stretch_table_van<T, D><<<dim3(pad8(table) + pad8(van_work)), dim3(256), (size_t)C::GROUPS * r * sizeof(int32_t), st>>>(
+  if (!ahead.table)
+    k_stretch_table_van<T, D><<<dim3(pad8(table) + pad8(van_work)), dim3(256), (size_t)C::GROUPS * r * sizeof(int32_t), st>>>(
       K, V, sr, fr, pa, d.S, n, r, (int32_t)d.p, make_fastdiv(blocks), pad8(table), table, ws_table(ws), first,
-      err_word(ws), zero, zero_per_slice, van, v0, make_fastdiv(van_tiles), van_work, pad8(van_work));
+      err_word(ws), zero, zero_per_slice, van, v0, van_div, van_work, pad8(van_work));
   const uint32_t rows = sr.rows.d, new_frames = ((uint32_t)n - sr.n0) / rows;
   const uint32_t old_tiles = (sr.n0 + TILE - 1) / TILE, cols = (rows + C::GROUPS - 1) / C::GROUPS;
   const uint32_t tiles = old_tiles + (new_frames + C::U - 1) / C::U * cols, work = slices * tiles;
   const uint32_t cv = cv_tau ? (uint32_t)(d.B * d.L) : 0u;
   const int32_t sure_past = (int32_t)std::max<int64_t>(0, (int64_t)n - (int64_t)r * d.p);
   k_stretch_tar<T, D><<<dim3(pad8(cv) + pad8(work)), dim3(256), 0, st>>>(
-      K, sr, pa, d.S, n, (int32_t)d.p, ws_table(ws), first, tar, err_word(ws), make_fastdiv(tiles), old_tiles,
+      K, sr, pa, waiting, d.S, n, (int32_t)d.p, ws_table(ws), first, tar, err_word(ws), make_fastdiv(tiles), old_tiles,
       make_fastdiv(cols), work, pad8(work), sure_past, van, (int32_t)d.H, cv ? cv_tau[0] : 0.0, cv ? cv_tau[1] : 0.0,
       cv ? cv_tau[2] : 0.0, ws_pool(ws, d), pad8(cv), cv);
   return launched();
 }
 
 ipv_status stretch_scores(const Dims& d, const char* K, const char* V, const Stretch& sr, const int32_t* fr,
-                          const int32_t* pa, int32_t n, int32_t r, float* tar, float* van, void* ws, hipStream_t st,
-                          int64_t zero_chunks, bool adjacent, const double* cv_tau, bool norms_known) {
+                          int32_t* pa, int32_t n, int32_t r, float* tar, float* van, void* ws, hipStream_t st,
+                          int64_t zero_chunks, bool adjacent, const double* cv_tau, bool norms_known, AheadDone ahead) {
 #define IPV_SCORES(T, DD)                                                                                           \
   if (d.D == DD)                                                                                                    \
-    return stretch_scores_t<T, DD>(d, K, V, sr, fr, pa, n, r, tar, van, ws, st, zero_chunks, adjacent, cv_tau, norms_known);
+    return stretch_scores_t<T, DD>(d, K, V, sr, fr, pa, n, r, tar, van, ws, st, zero_chunks, adjacent, cv_tau, norms_known, \
+                                   ahead);
   if (d.dtype == IPV_BF16) {
     IPV_SCORES(uint16_t, 32) IPV_SCORES(uint16_t, 64) IPV_SCORES(uint16_t, 128) IPV_SCORES(uint16_t, 256)
   } else {
     IPV_SCORES(float, 32) IPV_SCORES(float, 64) IPV_SCORES(float, 128) IPV_SCORES(float, 256)
   }
 #undef IPV_SCORES
+  return IPV_ERR_SHAPE;
+}
+
+// ------------------------------------------------------------ work of the next pass (ipv_ahead.hpp)
+// Whether the next pass's first launch goes out with this pass's selection: while
+// that leaves a quarter of the CUs at least (a selection block fills one, so with
+// more blocks nothing would run beside it), and up to 16 rows a thread (longer
+// slices' selections use every register of a CU).
+bool ahead_fits(const Dims& d, int32_t n, uint32_t mode) {
+  const int64_t groups = d.slices / ((mode & IPV_HEAD_SHARED) ? d.H : 1);
+  return groups <= kAheadGroups && n <= 16 * kSelThreads;
+}
+
+// The selection of a pass, with the first launch of the next one (next: its
+// rows, n_next of them; its new rows all lie in the frames).
+ipv_status select_ahead(const Dims& d, const float* tar, const float* van, int32_t* fr, int32_t* pa, int32_t n,
+                        const Stretch& sr, int32_t budget, int32_t tar_total, int32_t r, const Emit& em, const char* K,
+                        const char* V, const Stretch& next, int32_t n_next, int64_t next_chunks, AheadDone what,
+                        void* ws, hipStream_t st, uint32_t mode) {
+  const uint32_t lpr = (uint32_t)(d.D * d.elem / 16), slices = (uint32_t)d.slices;
+  const int32_t heads = (mode & IPV_HEAD_SHARED) ? (int32_t)d.H : 1;
+  const uint32_t tile = 256u / lpr * 4u * kAheadTiles, tiles = ((uint32_t)n_next - next.n0 + tile - 1) / tile;
+  const uint32_t per_block = kAheadThreads / lpr, blocks = ((uint32_t)d.p + per_block - 1) / per_block;
+  Ahead a{};
+  a.K = K;
+  a.V = V;
+  a.kind = kind_of(d.dtype == IPV_BF16, d.D);
+  a.st = next;
+  a.n = n_next;
+  a.r = r;
+  a.p = (int32_t)d.p;
+  a.norm = reinterpret_cast<float*>(pa);
+  a.tiles = make_fastdiv(tiles);
+  a.n_work = slices * tiles;
+  a.tile_blocks = pad8((a.n_work + 3) / 4);
+  if (what.table) {
+    a.table = ws_table(ws);
+    a.table_blocks = make_fastdiv(blocks);
+    a.table_real = slices * blocks;
+    a.table_padded = pad8(a.table_real);
+    a.first_recent = ws_first(ws, d);
+    a.zero = next_chunks > 0 ? ws_flags(ws, d) : nullptr;
+    a.zero_per_slice = (int32_t)(compact_parts(d) * walk_words(next_chunks));
+  }
+  a.sel_real = slices / (uint32_t)heads;
+  a.sel_padded = pad8(a.sel_real);
+  const dim3 grid(a.sel_padded + a.table_padded + a.tile_blocks), block(kAheadThreads);
+  const uint32_t tflip = flip_bits(mode, IPV_TAR_REVERSE), vflip = flip_bits(mode, IPV_VAN_REVERSE);
+  const int32_t rpt = (n + kSelThreads - 1) / kSelThreads;
+#define IPV_AHEAD(RPT)                                                                                                \
+  if (rpt <= RPT) {                                                                                                   \
+    if (d.S % 4 == 0)                                                                                                 \
+      k_select_ahead<RPT, true><<<grid, block, 0, st>>>(tar, van, fr, pa, d.S, n, budget, tar_total, r, err_word(ws), \
+                                                        heads, tflip, vflip, sr, em, a);                              \
+    else                                                                                                              \
+      k_select_ahead<RPT, false><<<grid, block, 0, st>>>(tar, van, fr, pa, d.S, n, budget, tar_total, r, err_word(ws), \
+                                                         heads, tflip, vflip, sr, em, a);                             \
+    return launched();                                                                                                \
+  }
+  IPV_AHEAD(4) IPV_AHEAD(8) IPV_AHEAD(12) IPV_AHEAD(16)
+#undef IPV_AHEAD
   return IPV_ERR_SHAPE;
 }
 
@@ -510,8 +585,6 @@ bool small_pass(const Dims& d, int32_t n, int32_t r, uint32_t mode, const double
   return !cv_tau && (mode & ~(uint32_t)(IPV_TAR_REVERSE | IPV_VAN_REVERSE)) == 0 && n <= kSmallRows && r <= 32 &&
          d.slices <= kComputeUnits && (int64_t)n * d.D * d.elem <= kSmallBytes;
 }
-
-uint32_t flip_bits(uint32_t mode, uint32_t bit) { return (mode & bit) ? 0xffffffffu : 0u; }
 
 template <typename T, int D, class ST>
 ipv_status small_pass_t(const Dims& d, void* K, void* V, int32_t* fr, int32_t* pa, int32_t n, const ST& rows,
@@ -950,6 +1023,9 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
     }
   }
   const std::vector<LoopStream> entry = ls;
+  // streams that entered the call alike stay alike, and share every launch
+  const bool alike = std::all_of(ls.begin(), ls.end(), [&](const LoopStream& s) { return s == ls[0]; });
+  AheadDone ahead;
   for (;;) {
     // the next frame at which a stream reaches the cap (frames [pending, f] are its new rows)
     int64_t f = INT64_MAX;
@@ -972,22 +1048,28 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
         int32_t* keep = keep_idx + b0 * ks;
         float* tr = at_stream(tar, b0, rs);
         float* vn = at_stream(van, b0, rs);
-        Stretch sr{};
-        sr.K = fk + b0 * nb;
-        sr.V = fv + b0 * nb;
-        sr.stride = frame_bytes;
-        sr.src = l.passes ? keep : nullptr;
-        sr.src_stride = budget;
-        sr.rows = make_fastdiv((uint32_t)rows);
-        sr.n0 = (uint32_t)l.n0;
-        sr.f0 = (uint32_t)l.pending;
-        sr.eoff = (uint32_t)l.pending * (uint32_t)rows - (uint32_t)l.n0;
-        sr.id0 = first_frame_id;
+        // the pass over l_n0 rows and the frames from `pending` on
+        auto stretch = [&](int32_t l_n0, int32_t pending, const int32_t* src) {
+          Stretch sr{};
+          sr.K = fk + b0 * nb;
+          sr.V = fv + b0 * nb;
+          sr.stride = frame_bytes;
+          sr.src = src;
+          sr.src_stride = budget;
+          sr.rows = make_fastdiv((uint32_t)rows);
+          sr.n0 = (uint32_t)l_n0;
+          sr.f0 = (uint32_t)pending;
+          sr.eoff = (uint32_t)pending * (uint32_t)rows - (uint32_t)l_n0;
+          sr.id0 = first_frame_id;
+          return sr;
+        };
+        const Stretch sr = stretch(l.n0, l.pending, l.passes ? keep : nullptr);
         int32_t* places = reinterpret_cast<int32_t*>(ws_table(ws));
         const bool small = small_pass(s, n, r, mode, cv_tau);
         if (!uniform && !small)
           IPV_TRY(stretch_scores(s, k, v, sr, fr, pa, n, r, tr, vn, ws, st, chunks, adjacent,
-                                 pool && !adjacent ? cv_tau : nullptr, l.passes > 0 && !pool));
+                                 pool && !adjacent ? cv_tau : nullptr, l.passes > 0 && !pool, ahead));
+        ahead = AheadDone{};
         if (pool) IPV_TRY(pool_d(s, cv_tau, vn, fr, pa, n, sr, nullptr, ws, st, !adjacent));
         const Emit em{fr,
                       pa,
@@ -998,7 +1080,15 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
         if (small)
           IPV_TRY(run_small_stretch(s, k, v, sr, fr, pa, n, budget, floor_share(alpha, budget), r, mode, tr, vn,
                                     l.passes > 0 ? sr.n0 : 0u, em, last, ws, st));
-        else
+        else if (alike && !last && !uniform && !pool && l.n0 <= budget && ahead_fits(s, n, mode)) {
+          const int64_t new_frames = fires_in(budget);
+          const bool then_last = l.passes + 2 == l.total;
+          ahead.norms = true;
+          ahead.table = !adjacent && new_frames > r;
+          IPV_TRY(select_ahead(s, tr, vn, fr, pa, n, sr, budget, floor_share(alpha, budget), r, em, k, v,
+                               stretch(budget, (int32_t)f + 1, nullptr), budget + (int32_t)new_frames * rows,
+                               then_last ? compact_chunks(budget) : 0, ahead, ws, st, mode));
+        } else
           IPV_TRY(select(s, tr, vn, fr, n, sr, budget, floor_share(alpha, budget), r, keep, err_word(ws), st, mode,
                        uniform && last ? ws_flags(ws, s) : nullptr, (int32_t)(compact_parts(s) * walk_words(chunks)),
                        em));

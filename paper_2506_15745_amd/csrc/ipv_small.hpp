@@ -142,7 +142,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_stretch(char* K, char* 
   const uint32_t cols = (rows + C::GROUPS - 1) / C::GROUPS;
   const uint32_t tiles = (((uint32_t)n - st.n0) / rows + C::U - 1) / C::U * cols;
   for (uint32_t t = tid / 256; t < tiles; t += kSmallThreads / 256)
-    stretch_tar_new<T, D>(st, S, (uint32_t)n, (uint32_t)p, table, rec, tar, slice, t / cols * C::U, t % cols, tid % 256);
+    stretch_tar_new<T, D>(st, S, (uint32_t)n, (uint32_t)p, table, rec, tar, nullptr, nullptr, slice, t / cols * C::U, t % cols,
+                          tid % 256);
   __syncthreads();
   if (gather) {
     em.src = places;

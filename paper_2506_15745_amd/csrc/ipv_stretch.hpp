@@ -59,7 +59,8 @@ __device__ __forceinline__ Raw16 load16_stream(const char* p) {
 // old row is then older than the window unless frame ids decrease, which the
 // selection reports), the key of recent frame j at position q is known without
 // a scan. Otherwise the window's metadata is scanned as in table_block.
-template <typename T, int D, int NT>
+// CLOSED: known on the host (slot may then be null).
+template <typename T, int D, int NT, bool CLOSED = false>
 __device__ __forceinline__ void stretch_table_block(const char* __restrict__ K, const Stretch& st,
                                                     const int32_t* __restrict__ frame_idx,
                                                     const int32_t* __restrict__ patch_idx, int64_t S, int32_t n,
@@ -73,7 +74,7 @@ __device__ __forceinline__ void stretch_table_block(const char* __restrict__ K, 
   const int64_t base = (int64_t)slice * S;
   const int32_t rows = (int32_t)st.rows.d, n0 = (int32_t)st.n0;
   const int32_t new_frames = (int32_t)fast_div((uint32_t)(n - n0), st.rows);
-  const bool closed = new_frames > r;
+  const bool closed = CLOSED || new_frames > r;
   if (closed) {
     if (q0 == 0 && tid == 0) first_recent[slice] = n - r * rows;
   } else {
@@ -148,33 +149,40 @@ __device__ __forceinline__ void stretch_table_block(const char* __restrict__ K, 
 
 // ---------------------------------------------------------------- value norms
 // A slice's norms to compute: rows [v0, n) (v0 = n0: the old rows' norms are in
-// van already; v0 = 0: all rows), 4 * GROUPS consecutive rows a tile.
-template <typename T, int D>
+// van already; v0 = 0: all rows), 4 * GROUPS consecutive rows a tile. TILES
+// tiles from x0 on are in flight together.
+template <typename T, int D, int TILES = 1>
 __device__ __forceinline__ void stretch_van_tile(const char* __restrict__ V, const Stretch& st, int64_t S, uint32_t n,
                                                  float* __restrict__ van, uint32_t slice, uint32_t x0, int tid) {
   using C = SweepCfg<T, D>;
   constexpr int LPR = C::LPR, GROUPS = C::GROUPS, U = C::U;
-  constexpr uint32_t RB = D * (uint32_t)sizeof(T);
+  constexpr uint32_t RB = D * (uint32_t)sizeof(T), ROWS = GROUPS * U;
   const uint32_t g = (uint32_t)(tid / LPR);
   const int lane = tid % LPR;
-  // lane l's own row is row l % 4 of its group; rows past n read row n - 1
-  const uint32_t xm = min(x0 + (uint32_t)(lane & 3) * GROUPS + g, n - 1);
-  const int32_t old = st.src && xm < st.n0 ? st.src[(int64_t)slice * st.src_stride + xm] : (int32_t)xm;
-  const int32_t s = xm < st.n0 ? old : ~(int32_t)(st.eoff + xm);
-  const uint64_t mine = reinterpret_cast<uint64_t>(row_place<RB>(V, st.V, st, S, slice, s));
   const uint32_t lo = (uint32_t)lane * 16u;
-  Raw16 v[U];
-  v[0] = load16_stream(dpp_ptr<0x00>(mine) + lo);
-  v[1] = load16_stream(dpp_ptr<0x55>(mine) + lo);
-  v[2] = load16_stream(dpp_ptr<0xAA>(mine) + lo);
-  v[3] = load16_stream(dpp_ptr<0xFF>(mine) + lo);
-  float part[U][1], tot[1];
+  Raw16 v[TILES][U];
 #pragma unroll
-  for (int u = 0; u < U; ++u) part[u][0] = Lane<T>::sumsq(v[u]);
-  reduce_scatter4<LPR, 1>(part, tot, lane);
-  constexpr int Q = (LPR > 16 ? 16 : LPR) / 4;
-  const uint32_t x = x0 + (uint32_t)scatter_row<LPR>(lane) * GROUPS + g;
-  if (lane < 16 && lane % Q == 0 && x < n) van[(int64_t)slice * S + x] = fast_sqrt(tot[0]);
+  for (int t = 0; t < TILES; ++t) {
+    // lane l's own row is row l % 4 of its group; rows past n read row n - 1
+    const uint32_t xm = min(x0 + t * ROWS + (uint32_t)(lane & 3) * GROUPS + g, n - 1);
+    const int32_t old = st.src && xm < st.n0 ? st.src[(int64_t)slice * st.src_stride + xm] : (int32_t)xm;
+    const int32_t s = xm < st.n0 ? old : ~(int32_t)(st.eoff + xm);
+    const uint64_t mine = reinterpret_cast<uint64_t>(row_place<RB>(V, st.V, st, S, slice, s));
+    v[t][0] = load16_stream(dpp_ptr<0x00>(mine) + lo);
+    v[t][1] = load16_stream(dpp_ptr<0x55>(mine) + lo);
+    v[t][2] = load16_stream(dpp_ptr<0xAA>(mine) + lo);
+    v[t][3] = load16_stream(dpp_ptr<0xFF>(mine) + lo);
+  }
+#pragma unroll
+  for (int t = 0; t < TILES; ++t) {
+    float part[U][1], tot[1];
+#pragma unroll
+    for (int u = 0; u < U; ++u) part[u][0] = Lane<T>::sumsq(v[t][u]);
+    reduce_scatter4<LPR, 1>(part, tot, lane);
+    constexpr int Q = (LPR > 16 ? 16 : LPR) / 4;
+    const uint32_t x = x0 + t * ROWS + (uint32_t)scatter_row<LPR>(lane) * GROUPS + g;
+    if (lane < 16 && lane % Q == 0 && x < n) van[(int64_t)slice * S + x] = fast_sqrt(tot[0]);
+  }
 }
 
 // Recent-key table blocks first, then the VaN tiles (as in k_table_van).
@@ -268,10 +276,18 @@ __device__ __forceinline__ void stretch_tar_old(const char* __restrict__ K, cons
 
 // New rows: GROUPS columns of 4 pending frames from `f`. A column's patch
 // position is the same in every frame, so its m vector is read once.
+// ahead (may be null): patch_idx, where the row's norm waits (ipv_ahead.hpp); it
+// goes to van, and the row's patch id takes its place.
+__device__ __forceinline__ void take_norm(int32_t* __restrict__ ahead, float* __restrict__ van, const Stretch& st,
+                                          int64_t at, uint32_t x) {
+  van[at] = __int_as_float(ahead[at]);
+  ahead[at] = st.patch_of(x);
+}
+
 template <typename T, int D>
 __device__ __forceinline__ void stretch_tar_new(const Stretch& st, int64_t S, uint32_t n, uint32_t p,
                                                 const float* __restrict__ table, uint32_t rec, float* __restrict__ tar,
-                                                uint32_t slice, uint32_t f, uint32_t colblock, int tid) {
+                                                int32_t* __restrict__ ahead, float* __restrict__ van, uint32_t slice, uint32_t f, uint32_t colblock, int tid) {
   using C = SweepCfg<T, D>;
   constexpr int EPL = C::EPL, LPR = C::LPR, GROUPS = C::GROUPS, U = C::U;
   constexpr uint32_t RB = D * (uint32_t)sizeof(T);
@@ -300,20 +316,24 @@ __device__ __forceinline__ void stretch_tar_new(const Stretch& st, int64_t S, ui
   reduce_scatter4<LPR, 2>(part, tot, lane);
   constexpr int Q = (LPR > 16 ? 16 : LPR) / 4;
   const uint32_t x = x0 + (uint32_t)scatter_row<LPR>(lane) * rows;
-  if (lane < 16 && lane % Q == 0 && x < n) tar[(int64_t)slice * S + x] = x < past_end ? tar_score(tot) : 0.f;
+  if (lane < 16 && lane % Q == 0 && x < n) {
+    const int64_t at = (int64_t)slice * S + x;
+    tar[at] = x < past_end ? tar_score(tot) : 0.f;
+    if (ahead) take_norm(ahead, van, st, at, x);
+  }
 }
 
 // The TaR launch of a pass, with the pooling CV blocks first (cv_padded = 0:
 // none). tiles: tiles per slice, the first old_tiles of them over the old rows.
 template <typename T, int D>
 __global__ __launch_bounds__(256) void k_stretch_tar(const char* __restrict__ K, Stretch st,
-                                                     const int32_t* __restrict__ patch_idx, int64_t S, int32_t n,
+                                                     const int32_t* patch_idx, int32_t* ahead, int64_t S, int32_t n,
                                                      int32_t p, const float* __restrict__ table,
                                                      const int32_t* __restrict__ first_recent, float* __restrict__ tar,
                                                      uint32_t* err, FastDiv tiles, uint32_t old_tiles, FastDiv col_blocks,
                                                      uint32_t n_work, uint32_t tile_blocks, int32_t sure_past,
-                                                     const float* __restrict__ van, int32_t H, double tau1, double tau2,
-                                                     double tau3, int32_t* __restrict__ pool_ws, uint32_t cv_padded,
+                                                     float* van, int32_t H, double tau1, double tau2, double tau3,
+                                                     int32_t* __restrict__ pool_ws, uint32_t cv_padded,
                                                      uint32_t cv_real) {
   __shared__ double red[256 / kWave];
   if (blockIdx.x < cv_padded) {
@@ -334,7 +354,8 @@ __global__ __launch_bounds__(256) void k_stretch_tar(const char* __restrict__ K,
     const uint32_t fb = fast_div(t - old_tiles, col_blocks), cb = t - old_tiles - fb * col_blocks.d;
     const bool tail = (int64_t)st.n0 + (int64_t)(fb + 1) * C::U * st.rows.d > sure_past;
     const uint32_t rec = tail ? (uint32_t)first_recent[slice] : (uint32_t)n;
-    stretch_tar_new<T, D>(st, S, (uint32_t)n, (uint32_t)p, table, rec, tar, slice, fb * C::U, cb, threadIdx.x);
+    stretch_tar_new<T, D>(st, S, (uint32_t)n, (uint32_t)p, table, rec, tar, ahead, van, slice, fb * C::U, cb,
+                          threadIdx.x);
   }
 }
 
@@ -364,8 +385,8 @@ template <typename T, int D>
 __global__ __launch_bounds__(256) void k_stretch_adjacent(const char* __restrict__ K, Stretch st,
                                                           const int32_t* __restrict__ prev, int64_t S, int32_t n,
                                                           const int32_t* __restrict__ first_recent,
-                                                          float* __restrict__ tar, FastDiv tiles, uint32_t n_work,
-                                                          uint32_t tile_blocks) {
+                                                          float* __restrict__ tar, int32_t* ahead, float* van,
+                                                          FastDiv tiles, uint32_t n_work, uint32_t tile_blocks) {
   using C = SweepCfg<T, D>;
   constexpr int LPR = C::LPR, GROUPS = C::GROUPS, U = C::U;
   constexpr uint32_t RB = D * (uint32_t)sizeof(T);
@@ -407,7 +428,10 @@ __global__ __launch_bounds__(256) void k_stretch_adjacent(const char* __restrict
   }
   if (lane < U) {
     const uint32_t x = x0 + lane * GROUPS + g;
-    if (x < (uint32_t)n) tar[base + x] = lane == 0 ? tsc[0] : lane == 1 ? tsc[1] : lane == 2 ? tsc[2] : tsc[3];
+    if (x < (uint32_t)n) {
+      tar[base + x] = lane == 0 ? tsc[0] : lane == 1 ? tsc[1] : lane == 2 ? tsc[2] : tsc[3];
+      if (ahead && x >= st.n0) take_norm(ahead, van, st, base + x, x);
+    }
   }
 }
 
