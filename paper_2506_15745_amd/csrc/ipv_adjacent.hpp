@@ -36,6 +36,12 @@ constexpr int kPrevMaxPositions = 8192;
 // The chunk's frame ids are double-buffered in LDS; a chunk costs six
 // barriers and no global-memory round trip (the next chunk's loads are in
 // flight meanwhile). One slice's walk is one block of kPrevThreads threads.
+//
+// The rows of a stretch's pending frames after the first need no walk: a frame
+// holds the same positions as the one before it, so prev(x) = x - rows. The
+// walk ends with the first pending frame (four chunks instead of seven for a
+// pass of 16 new frames over 3136 old rows, one for a pass of new frames only):
+// the launch with the walks 30.6 -> 23.7 us on average over those two passes.
 template <class ST>
 __device__ __forceinline__ void prev_rows_block(int64_t slice, const int32_t* __restrict__ frame_idx,
                                                 const int32_t* __restrict__ patch_idx, int64_t S, int32_t n,
@@ -64,6 +70,13 @@ __device__ __forceinline__ void prev_rows_block(int64_t slice, const int32_t* __
   auto frame_at = [&](int64_t x) { return row_frame(st, x, frame_idx[base + x]); };
   auto patch_at = [&](int64_t x) { return row_patch(st, x, patch_idx[base + x]); };
   const int64_t thr = (int64_t)frame_at((int64_t)n - 1) - r + 1;
+  if constexpr (ST::kNew) {
+    const int32_t rows = (int32_t)st.rows.d, walk = min(n, (int32_t)st.n0 + rows);
+    for (int32_t x = walk + tid; x < n; x += NT) prev[base + x] = (int64_t)st.frame_of(x) < thr ? x - rows : -1;
+    const int64_t first = (int64_t)n - (int64_t)r * rows;  // first row of the oldest recent pending frame
+    if (tid == 0 && first >= walk) first_recent[slice] = (int32_t)first;
+    n = walk;
+  }
   uint32_t ebits = 0;
   int32_t nf = frame_at(min((int64_t)tid, (int64_t)n - 1));
   int32_t np = patch_at(min((int64_t)tid, (int64_t)n - 1));
