@@ -26,7 +26,7 @@ struct Ahead {
   Stretch st;         // the next pass's
   int32_t n, r, p;
   float* norm;        // patch_idx as floats, or null: no norms to compute
-  FastDiv tiles;      // norm tiles (kAheadTiles of them count as one) per slice
+  FastDiv slices;
   uint32_t n_work, tile_blocks;
   float* table;       // null: no table
   FastDiv table_blocks;
@@ -66,10 +66,9 @@ __device__ __forceinline__ void ahead_block(const Ahead& a, const int32_t* frame
   }
   const uint32_t logical = xcd_logical_id(i - a.table_padded, a.tile_blocks) * 4u + threadIdx.x / 256u;
   if (logical >= a.n_work) return;
-  const uint32_t slice = fast_div(logical, a.tiles);
+  const uint32_t t = fast_div(logical, a.slices), slice = logical - t * a.slices.d;
   stretch_van_tile<T, D, kAheadTiles>(a.V, a.st, S, (uint32_t)a.n, a.norm, slice,
-                                      a.st.n0 + (logical - slice * a.tiles.d) * (C::GROUPS * C::U * kAheadTiles),
-                                      threadIdx.x % 256u);
+                                      a.st.n0 + t * (C::GROUPS * C::U * kAheadTiles), threadIdx.x % 256u);
 }
 
 // Selection blocks first (those at or past sel_real return at once); sel_padded

@@ -448,15 +448,17 @@ ipv_status stretch_scores_t(const Dims& d, const char* K, const char* V, const S
   if (!ahead.table)
     k_stretch_table_van<T, D><<<dim3(pad8(table) + pad8(van_work)), dim3(256), (size_t)C::GROUPS * r * sizeof(int32_t), st>>>(
       K, V, sr, fr, pa, d.S, n, r, (int32_t)d.p, make_fastdiv(blocks), pad8(table), table, ws_table(ws), first,
-      err_word(ws), zero, zero_per_slice, van, v0, van_div, van_work, pad8(van_work));
+      err_word(ws), zero, zero_per_slice, van, v0, van_div, make_fastdiv(slices), van_work, pad8(van_work));
   const uint32_t rows = sr.rows.d, new_frames = ((uint32_t)n - sr.n0) / rows;
   const uint32_t old_tiles = (sr.n0 + TILE - 1) / TILE, cols = (rows + C::GROUPS - 1) / C::GROUPS;
-  const uint32_t tiles = old_tiles + (new_frames + C::U - 1) / C::U * cols, work = slices * tiles;
+  const uint32_t tiles = old_tiles + (new_frames + C::U - 1) / C::U * cols;
+  const uint32_t group = sr.n0 == 0 ? kSliceGroup : 0u;
+  const uint32_t work = ((slices + (1u << group) - 1) >> group << group) * tiles;
   const uint32_t cv = cv_tau ? (uint32_t)(d.B * d.L) : 0u;
   const int32_t sure_past = (int32_t)std::max<int64_t>(0, (int64_t)n - (int64_t)r * d.p);
   k_stretch_tar<T, D><<<dim3(pad8(cv) + pad8(work)), dim3(256), 0, st>>>(
       K, sr, pa, waiting, d.S, n, (int32_t)d.p, ws_table(ws), first, tar, err_word(ws), make_fastdiv(tiles), old_tiles,
-      make_fastdiv(cols), work, pad8(work), sure_past, van, (int32_t)d.H, cv ? cv_tau[0] : 0.0, cv ? cv_tau[1] : 0.0,
+      make_fastdiv(cols), work, pad8(work), slices, group, sure_past, van, (int32_t)d.H, cv ? cv_tau[0] : 0.0, cv ? cv_tau[1] : 0.0,
       cv ? cv_tau[2] : 0.0, ws_pool(ws, d), pad8(cv), cv);
   return launched();
 }
@@ -506,7 +508,7 @@ ipv_status select_ahead(const Dims& d, const float* tar, const float* van, int32
   a.r = r;
   a.p = (int32_t)d.p;
   a.norm = reinterpret_cast<float*>(pa);
-  a.tiles = make_fastdiv(tiles);
+  a.slices = make_fastdiv(slices);
   a.n_work = slices * tiles;
   a.tile_blocks = pad8((a.n_work + 3) / 4);
   if (what.table) {
