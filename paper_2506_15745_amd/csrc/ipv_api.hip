@@ -1068,6 +1068,7 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
         const Stretch sr = stretch(l.n0, l.pending, l.passes ? keep : nullptr);
         int32_t* places = reinterpret_cast<int32_t*>(ws_table(ws));
         const bool small = small_pass(s, n, r, mode, cv_tau);
+        const int32_t new_frames = (int32_t)fires_in(budget), n_next = budget + new_frames * rows;  // the next pass's
         if (!uniform && !small)
           IPV_TRY(stretch_scores(s, k, v, sr, fr, pa, n, r, tr, vn, ws, st, chunks, adjacent,
                                  pool && !adjacent ? cv_tau : nullptr, l.passes > 0 && !pool, ahead));
@@ -1082,13 +1083,13 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
         if (small)
           IPV_TRY(run_small_stretch(s, k, v, sr, fr, pa, n, budget, floor_share(alpha, budget), r, mode, tr, vn,
                                     l.passes > 0 ? sr.n0 : 0u, em, last, ws, st));
-        else if (alike && !last && !uniform && !pool && l.n0 <= budget && ahead_fits(s, n, mode)) {
-          const int64_t new_frames = fires_in(budget);
+        else if (alike && !last && !uniform && !pool && l.n0 <= budget && ahead_fits(s, n, mode) &&
+                 !small_pass(s, n_next, r, mode, cv_tau)) {
           const bool then_last = l.passes + 2 == l.total;
           ahead.norms = true;
           ahead.table = !adjacent && new_frames > r;
           IPV_TRY(select_ahead(s, tr, vn, fr, pa, n, sr, budget, floor_share(alpha, budget), r, em, k, v,
-                               stretch(budget, (int32_t)f + 1, nullptr), budget + (int32_t)new_frames * rows,
+                               stretch(budget, (int32_t)f + 1, nullptr), n_next,
                                then_last ? compact_chunks(budget) : 0, ahead, ws, st, mode));
         } else
           IPV_TRY(select(s, tr, vn, fr, n, sr, budget, floor_share(alpha, budget), r, keep, err_word(ws), st, mode,

@@ -334,9 +334,9 @@ __device__ __forceinline__ void stretch_tar_new(const Stretch& st, int64_t S, ui
 // nearby memory when neighbouring slices take the same tile in turn. The TaR
 // tiles of a pass without old rows go 8 slices at a time, whose m tables (100 KB
 // each for a 14x14 grid and 128 elements) fit an XCD's 4 MB of L2: 973 -> 933 us on
-// the 72B-class cache (16 at a time 978 us). Old rows are strewn over their slice's table, and only
-// that one stays in L2 with them: one slice at a time (75 us a pass of the 16x16
-// video, 78 us with 8 in turn).
+// the 72B-class cache (16 at a time 978 us). Old rows are strewn over their
+// slice's table, and only that one stays in L2 with them: one slice at a time
+// (75 us a pass of the 16x16 video, 78 us with 8 in turn).
 constexpr uint32_t kSliceGroup = 3;  // log2
 
 // The TaR launch of a pass, with the pooling CV blocks first (cv_padded = 0:

@@ -43,6 +43,8 @@ CASES = {
     "ahead-193-selections": (193, 1, 32, (6, 7), 42, (0,), 40, 600, 300, 2, 642, "bf16", 0, None),
     "ahead-narrow-frames": (1, 2, 64, (8, 8), 41, (20, 20), 60, 900, 400, 2, 943, "f32", ipv.VAN_REVERSE, None),
     "ahead-rows-above-the-budget": (1, 2, 128, (7, 7), 49, (900,), 80, 1000, 500, 2, 1049, "bf16", 0, None),
+    # the first pass has 260 rows, the later ones 250 and go out as one launch each
+    "ahead-then-small": (1, 2, 64, (4, 5), 20, (0,), 40, 250, 230, 2, 270, "bf16", 0, None),
     "ahead-adjacent": (2, 2, 256, (9, 13), 117, (0,), 60, 1700, 800, 3, 1819, "f32", ipv.TAR_ADJACENT, None),
     "ahead-adjacent-shared": (3, 2, 64, (9, 13), 117, (0, 0), 60, 1700, 1500, 4, 1817, "bf16",
                         ipv.TAR_ADJACENT | ipv.HEAD_SHARED, None),
