@@ -27,9 +27,10 @@
  * A cache holds B streams x L layers x H KV heads; each (b, l, h) "slice" has
  * a row capacity S of which rows [0, n_tokens[b]) are valid. n_tokens is a
  * HOST array of B row counts (streams fill at their own pace); a stream with
- * 0 rows is left alone by every call except ipv_append. The work is launched
- * once per maximal run of consecutive streams with the same count, so a batch
- * at one fill level is one launch per kernel. All row-major:
+ * 0 rows is left alone by every call except ipv_append. Consecutive streams
+ * share a launch while a grid for the largest of their counts has rows for at
+ * least half of its tiles (at most 64 streams of different counts together), so
+ * a batch at one fill level is one launch per kernel. All row-major:
  *   K, V        [B, L, H, S, D] elements of `dtype` (bf16 or fp32), device
  *   frame_idx   [B, L, H, S] int32, device: frame id of each row
  *   patch_idx   [B, L, H, S] int32, device: patch position in [0, grid_h*grid_w)
