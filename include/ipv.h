@@ -30,7 +30,9 @@
  * 0 rows is left alone by every call except ipv_append. Consecutive streams
  * share a launch while a grid for the largest of their counts has rows for at
  * least half of its tiles (at most 64 streams of different counts together), so
- * a batch at one fill level is one launch per kernel. All row-major:
+ * a batch at one fill level is one launch per kernel (ipv_append: streams of one
+ * count; ipv_ckv_stream: streams of one count that were compressed at the same
+ * frame last, or not yet). All row-major:
  *   K, V        [B, L, H, S, D] elements of `dtype` (bf16 or fp32), device
  *   frame_idx   [B, L, H, S] int32, device: frame id of each row
  *   patch_idx   [B, L, H, S] int32, device: patch position in [0, grid_h*grid_w)

@@ -540,8 +540,8 @@ ipv_status select_ahead(const Dims& d, const float* tar, const float* van, int32
   return IPV_ERR_SHAPE;
 }
 
-// src: places of the budget rows that stay, [slices, S]; n_entry: rows the
-// cache held before the call
+// src: places of the budget rows that stay, [slices, S]; n_entry: most rows a
+// slice held before the call
 template <int RB>
 ipv_status stretch_gather_t(const Dims& d, void* K, void* V, const Stretch& sr, const int32_t* src, int32_t n_entry,
                             int32_t budget, void* ws, hipStream_t st) {
@@ -826,14 +826,15 @@ ipv_status append_run(const Dims& d, int64_t b, int64_t e, void* K, void* V, int
   return launched();
 }
 
-// A stream's place in a call of the continual-compression loop.
+// A stream's place in a call of the continual-compression loop. Streams with the
+// same rows and the same pending frames are alike for the rest of the call,
+// whatever counts they entered it with: the passes they have left and, once they
+// have had one (pending > 0), where their rows are found follow from these two.
 struct LoopStream {
   int32_t n0;       // rows before its pending frames
   int32_t pending;  // first frame of the call that is not in a pass yet
-  int32_t passes, total;  // passes so far and in the whole call
-  bool operator==(const LoopStream& o) const {
-    return n0 == o.n0 && pending == o.pending && passes == o.passes && total == o.total;
-  }
+  int32_t left;     // passes left
+  bool operator==(const LoopStream& o) const { return n0 == o.n0 && pending == o.pending; }
 };
 
 // fn(b, e) for every maximal run [b, e) of streams that are alike and satisfy want
@@ -1016,90 +1017,86 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
   auto fires_in = [&](int32_t n) { return (mem_cap - n + rows - 1) / rows; };  // frames until the cap, the last included
   std::vector<LoopStream> ls((size_t)d.B);
   for (int64_t b = 0; b < d.B; ++b) {
-    ls[b] = {n_tokens[b], 0, 0, 0};
+    ls[b] = {n_tokens[b], 0, 0};
     // a budget equal to the cap fires once: the checks let no frame follow that pass
     const int64_t later = fires_in(budget);
     for (int64_t f = fires_in(n_tokens[b]); f <= n_frames; f += later) {
-      ++ls[b].total;
+      ++ls[b].left;
       if (later < 1) break;
     }
   }
-  const std::vector<LoopStream> entry = ls;
-  // streams that entered the call alike stay alike, and share every launch
-  const bool alike = std::all_of(ls.begin(), ls.end(), [&](const LoopStream& s) { return s == ls[0]; });
   AheadDone ahead;
   for (;;) {
     // the next frame at which a stream reaches the cap (frames [pending, f] are its new rows)
     int64_t f = INT64_MAX;
     for (const LoopStream& s : ls)
-      if (s.passes < s.total) f = std::min<int64_t>(f, (int64_t)s.pending + fires_in(s.n0) - 1);
+      if (s.left > 0) f = std::min<int64_t>(f, (int64_t)s.pending + fires_in(s.n0) - 1);
     if (f == INT64_MAX) break;
-    auto fires = [&](const LoopStream& s) { return s.passes < s.total && (int64_t)s.pending + fires_in(s.n0) - 1 == f; };
-    IPV_TRY(for_alike(ls, fires, [&](int64_t b0, int64_t b1) -> ipv_status {
-      for (int64_t e; b0 < b1; b0 = e) {  // streams that entered the call alike, too
-        for (e = b0 + 1; e < b1 && entry[e].n0 == entry[b0].n0;) ++e;
-        const Dims s = sub_batch(d, e - b0);
-        const LoopStream l = ls[b0];
-        const bool last = l.passes + 1 == l.total;
-        const int32_t n = l.n0 + (int32_t)(f + 1 - l.pending) * rows;
-        const int64_t chunks = last ? compact_chunks(budget) : 0;
-        char* k = static_cast<char*>(K) + b0 * kb;
-        char* v = static_cast<char*>(V) + b0 * kb;
-        int32_t* fr = frame_idx + b0 * rs;
-        int32_t* pa = patch_idx + b0 * rs;
-        int32_t* keep = keep_idx + b0 * ks;
-        float* tr = at_stream(tar, b0, rs);
-        float* vn = at_stream(van, b0, rs);
-        // the pass over l_n0 rows and the frames from `pending` on
-        auto stretch = [&](int32_t l_n0, int32_t pending, const int32_t* src) {
-          Stretch sr{};
-          sr.K = fk + b0 * nb;
-          sr.V = fv + b0 * nb;
-          sr.stride = frame_bytes;
-          sr.src = src;
-          sr.src_stride = budget;
-          sr.rows = make_fastdiv((uint32_t)rows);
-          sr.n0 = (uint32_t)l_n0;
-          sr.f0 = (uint32_t)pending;
-          sr.eoff = (uint32_t)pending * (uint32_t)rows - (uint32_t)l_n0;
-          sr.id0 = first_frame_id;
-          return sr;
-        };
-        const Stretch sr = stretch(l.n0, l.pending, l.passes ? keep : nullptr);
-        int32_t* places = reinterpret_cast<int32_t*>(ws_table(ws));
-        const bool small = small_pass(s, n, r, mode, cv_tau);
-        const int32_t new_frames = (int32_t)fires_in(budget), n_next = budget + new_frames * rows;  // the next pass's
-        if (!uniform && !small)
-          IPV_TRY(stretch_scores(s, k, v, sr, fr, pa, n, r, tr, vn, ws, st, chunks, adjacent,
-                                 pool && !adjacent ? cv_tau : nullptr, l.passes > 0 && !pool, ahead));
-        ahead = AheadDone{};
-        if (pool) IPV_TRY(pool_d(s, cv_tau, vn, fr, pa, n, sr, nullptr, ws, st, !adjacent));
-        const Emit em{fr,
-                      pa,
-                      last ? places : keep,
-                      last ? s.S : budget,
-                      last || pool || uniform ? nullptr : vn,
-                      last ? keep : nullptr};
-        if (small)
-          IPV_TRY(run_small_stretch(s, k, v, sr, fr, pa, n, budget, floor_share(alpha, budget), r, mode, tr, vn,
-                                    l.passes > 0 ? sr.n0 : 0u, em, last, ws, st));
-        else if (alike && !last && !uniform && !pool && l.n0 <= budget && ahead_fits(s, n, mode) &&
-                 !small_pass(s, n_next, r, mode, cv_tau)) {
-          const bool then_last = l.passes + 2 == l.total;
-          ahead.norms = true;
-          ahead.table = !adjacent && new_frames > r;
-          IPV_TRY(select_ahead(s, tr, vn, fr, pa, n, sr, budget, floor_share(alpha, budget), r, em, k, v,
-                               stretch(budget, (int32_t)f + 1, nullptr), n_next,
-                               then_last ? compact_chunks(budget) : 0, ahead, ws, st, mode));
-        } else
-          IPV_TRY(select(s, tr, vn, fr, n, sr, budget, floor_share(alpha, budget), r, keep, err_word(ws), st, mode,
+    auto fires = [&](const LoopStream& s) { return s.left > 0 && (int64_t)s.pending + fires_in(s.n0) - 1 == f; };
+    IPV_TRY(for_alike(ls, fires, [&](int64_t b0, int64_t e) -> ipv_status {
+      const Dims s = sub_batch(d, e - b0);
+      const LoopStream l = ls[b0];
+      const bool last = l.left == 1;
+      const int32_t n = l.n0 + (int32_t)(f + 1 - l.pending) * rows;
+      const int64_t chunks = last ? compact_chunks(budget) : 0;
+      char* k = static_cast<char*>(K) + b0 * kb;
+      char* v = static_cast<char*>(V) + b0 * kb;
+      int32_t* fr = frame_idx + b0 * rs;
+      int32_t* pa = patch_idx + b0 * rs;
+      int32_t* keep = keep_idx + b0 * ks;
+      float* tr = at_stream(tar, b0, rs);
+      float* vn = at_stream(van, b0, rs);
+      // the pass over l_n0 rows and the frames from `pending` on
+      auto stretch = [&](int32_t l_n0, int32_t pending, const int32_t* src) {
+        Stretch sr{};
+        sr.K = fk + b0 * nb;
+        sr.V = fv + b0 * nb;
+        sr.stride = frame_bytes;
+        sr.src = src;
+        sr.src_stride = budget;
+        sr.rows = make_fastdiv((uint32_t)rows);
+        sr.n0 = (uint32_t)l_n0;
+        sr.f0 = (uint32_t)pending;
+        sr.eoff = (uint32_t)pending * (uint32_t)rows - (uint32_t)l_n0;
+        sr.id0 = first_frame_id;
+        return sr;
+      };
+      const Stretch sr = stretch(l.n0, l.pending, l.pending ? keep : nullptr);
+      int32_t* places = reinterpret_cast<int32_t*>(ws_table(ws));
+      const bool small = small_pass(s, n, r, mode, cv_tau);
+      const int32_t new_frames = (int32_t)fires_in(budget), n_next = budget + new_frames * rows;  // the next pass's
+      if (!uniform && !small)
+        IPV_TRY(stretch_scores(s, k, v, sr, fr, pa, n, r, tr, vn, ws, st, chunks, adjacent,
+                               pool && !adjacent ? cv_tau : nullptr, l.pending > 0 && !pool, ahead));
+      ahead = AheadDone{};
+      if (pool) IPV_TRY(pool_d(s, cv_tau, vn, fr, pa, n, sr, nullptr, ws, st, !adjacent));
+      const Emit em{fr,
+                    pa,
+                    last ? places : keep,
+                    last ? s.S : budget,
+                    last || pool || uniform ? nullptr : vn,
+                    last ? keep : nullptr};
+      if (small)
+        IPV_TRY(run_small_stretch(s, k, v, sr, fr, pa, n, budget, floor_share(alpha, budget), r, mode, tr, vn,
+                                  l.pending > 0 ? sr.n0 : 0u, em, last, ws, st));
+      else if (s.B == d.B && !last && !uniform && !pool && l.n0 <= budget && ahead_fits(s, n, mode) &&
+               !small_pass(s, n_next, r, mode, cv_tau)) {  // the whole batch: it stays alike, so the next pass is its
+        const bool then_last = l.left == 2;
+        ahead.norms = true;
+        ahead.table = !adjacent && new_frames > r;
+        IPV_TRY(select_ahead(s, tr, vn, fr, pa, n, sr, budget, floor_share(alpha, budget), r, em, k, v,
+                             stretch(budget, (int32_t)f + 1, nullptr), n_next,
+                             then_last ? compact_chunks(budget) : 0, ahead, ws, st, mode));
+      } else
+        IPV_TRY(select(s, tr, vn, fr, n, sr, budget, floor_share(alpha, budget), r, keep, err_word(ws), st, mode,
                        uniform && last ? ws_flags(ws, s) : nullptr, (int32_t)(compact_parts(s) * walk_words(chunks)),
                        em));
-        if (last && !small) IPV_TRY(stretch_gather(s, k, v, sr, places, entry[b0].n0, budget, ws, st));
-        for (int64_t b = b0; b < e; ++b) {
-          ls[b] = {budget, (int32_t)f + 1, l.passes + 1, l.total};
-          ++passes[b];
-        }
+      // only the gather asks how many rows the streams entered the call with: the most of them bounds its waits
+      const int32_t n_entry = *std::max_element(n_tokens + b0, n_tokens + e);
+      if (last && !small) IPV_TRY(stretch_gather(s, k, v, sr, places, n_entry, budget, ws, st));
+      for (int64_t b = b0; b < e; ++b) {
+        ls[b] = {budget, (int32_t)f + 1, l.left - 1};
+        ++passes[b];
       }
       return IPV_OK;
     }));

@@ -19,6 +19,9 @@ CASES = {
     "few-new-frames": (1, 2, 64, (5, 5), 25, (0, 75), 40, 301, 270, 3, 333, "f32", 0, None),
     # frames of fewer rows than the grid; streams with passes at different frames; one that never fires
     "partial-frames": (2, 1, 128, (6, 7), 31, (0, 310, 42), 37, 700, 400, 4, 731, "bf16", 0, None),
+    # streams that enter with different counts (none, too) and are alike from a later pass on, the last one's gather included
+    "entries-join": (2, 2, 128, (7, 7), 49, (0, 1760, 1775), 60, 2000, 1600, 4, 2052, "bf16", 0, None),
+    "entries-join-adjacent": (1, 2, 64, (7, 7), 49, (1775, 0, 1760), 70, 2000, 1600, 2, 2051, "f32", ipv.TAR_ADJACENT, None),
     "pooled": (4, 2, 64, (4, 4), 16, (0, 64), 30, 130, 70, 2, 146, "bf16", ipv.VAN_REVERSE, (0.3, 0.5, 0.7)),
     "adjacent": (2, 2, 128, (9, 13), 117, (234,), 40, 1300, 700, 3, 1417, "bf16", ipv.TAR_ADJACENT, None),
     "adjacent-shared-f32": (2, 4, 256, (3, 5), 15, (15,), 40, 150, 91, 2, 165, "f32",
