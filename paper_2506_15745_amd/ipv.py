@@ -215,7 +215,8 @@ def _pass_ptrs(K, V, frame_idx, patch_idx, tar, van, keep_idx, budget, ws, grid_
     """(shape, device, K, V, frame_idx, patch_idx, tar, van, keep_idx, ws) as
     the library takes them, or None when a check fails or a buffer is missing:
     the checks one by one then say whether that is an error and which."""
-    if tar is None or van is None or keep_idx is None or ws is None:
+    if (V is None or frame_idx is None or patch_idx is None or tar is None or van is None or keep_idx is None or ws is None
+            or type(grid_h) is not int or type(grid_w) is not int):  # _shape keeps results by value: 4.0 is equal to 4
         return None
     kd, dev, kv = K.dtype, K.get_device(), K.shape
     code = BF16 if kd is torch.bfloat16 else F32 if kd is torch.float32 else -1
@@ -399,8 +400,8 @@ def ipv_ckv_step(K, V, frame_idx, patch_idx, n_tokens, K_new, V_new, frame_id, f
     rows. Returns (row counts, whether each stream's pass ran): ints for an
     int n_tokens (every stream then behaves alike), else lists."""
     got = _pass_ptrs(K, V, frame_idx, patch_idx, tar, van, keep_idx, budget, ws, grid_h, grid_w)
-    new = K_new.shape
-    if (got is not None and len(new) == 5 and V_new.shape == new and K_new.dtype is K.dtype and V_new.dtype is K.dtype
+    new = K_new.shape if got is not None else ()
+    if (len(new) == 5 and V_new.shape == new and K_new.dtype is K.dtype and V_new.dtype is K.dtype
             and (new[0], new[1], new[2], new[4]) == (got[0].streams, got[0].layers, got[0].kv_heads, got[0].head_dim)
             and K_new.get_device() == got[1] and V_new.get_device() == got[1] and K_new.is_contiguous()
             and V_new.is_contiguous()):
@@ -412,7 +413,7 @@ def ipv_ckv_step(K, V, frame_idx, patch_idx, n_tokens, K_new, V_new, frame_id, f
         _check_new_rows(K, K_new, V_new)
         s, k, v, fr, pa, tr, vn, keep, w = _checked_ptrs(K, V, frame_idx, patch_idx, tar, van, keep_idx, budget, ws,
                                                          grid_h, grid_w, mode, optional=True)
-        kn, vnew = _ptr(K_new), _ptr(V_new)
+        new, kn, vnew = K_new.shape, _ptr(K_new), _ptr(V_new)
     tau = None if cv_tau is None else (ctypes.c_double * 3)(*cv_tau)
     out = (ctypes.c_int32 * s.streams)
     n_out, comp = out(), out()

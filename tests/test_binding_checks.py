@@ -88,3 +88,49 @@ def test_append_and_loop_check_new_rows():
     Fk = torch.zeros(3, B, L, H, 16, D, dtype=torch.float32)
     assert status(ipv.ipv_ckv_stream, b["K"], b["V"], b["fr"], b["pa"], 0, Fk, Fk, 0, 48, C, 0.5, 1, None,
                   b["tar"], b["van"], b["keep"], b["ws"], GH, GW) == ipv.ERR_DTYPE
+
+
+class OnGpu:
+    """Answers the binding's questions as a contiguous GPU tensor would."""
+    is_cuda, device = True, torch.device("cuda:0")
+
+    def __init__(self, *shape, dtype=torch.float32):
+        self.shape, self.dtype = torch.Size(shape), dtype
+
+    def dim(self):
+        return len(self.shape)
+
+    def get_device(self):
+        return 0
+
+    def is_contiguous(self):
+        return True
+
+    def data_ptr(self):
+        return 4096
+
+
+def gpu_buffers():
+    rows, i32, bf16 = (1, 2, 2, 64), torch.int32, torch.bfloat16
+    return [OnGpu(*rows, 32, dtype=bf16), OnGpu(*rows, 32, dtype=bf16), OnGpu(*rows, dtype=i32), OnGpu(*rows, dtype=i32),
+            OnGpu(*rows), OnGpu(*rows), OnGpu(1, 2, 2, 32, dtype=i32)]
+
+
+@pytest.mark.parametrize("missing", [1, 2, 3])  # V, frame_idx, patch_idx
+def test_missing_buffers_of_a_gpu_cache_are_refused(missing):
+    b = gpu_buffers()
+    b[missing] = None
+    with pytest.raises(ipv.IpvError) as e:
+        ipv._checked_ptrs(*b, 32, OnGpu(1 << 20, dtype=torch.uint8), 4, 4, 0)
+    assert e.value.status == ipv.ERR_NULL
+
+
+def test_a_grid_is_read_by_its_value_and_type_in_each_call():
+    run = lambda g: ipv._checked_ptrs(*gpu_buffers(), 32, OnGpu(1 << 20, dtype=torch.uint8), g, 4, 0)[0].grid_h  # noqa: E731
+    assert run(4) == 4 and run(torch.tensor(4)) == 4
+    with pytest.raises(TypeError):
+        run(4.0)
+    changing = torch.tensor(4)
+    assert run(changing) == 4
+    changing.fill_(5)
+    assert run(changing) == 5

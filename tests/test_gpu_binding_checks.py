@@ -1,5 +1,6 @@
 """The binding reads a pass's whole buffer set at once when everything fits;
 what does not fit is refused with the same status as on host tensors."""
+import numpy as np
 import pytest
 import torch
 
@@ -47,6 +48,9 @@ BAD = {
     "fr-float": ("fr", lambda t: t.float(), ipv.ERR_DTYPE),
     "pa-host": ("pa", lambda t: t.cpu(), ipv.ERR_ARG),
     "ws-host": ("ws", lambda t: t.cpu(), ipv.ERR_ARG),
+    "V-none": ("V", lambda t: None, ipv.ERR_NULL),
+    "fr-none": ("fr", lambda t: None, ipv.ERR_NULL),
+    "pa-none": ("pa", lambda t: None, ipv.ERR_NULL),
     "ws-small": ("ws", lambda t: t[:512].clone(), ipv.ERR_WORKSPACE),
 }
 
@@ -75,6 +79,23 @@ def test_mismatched_frames_are_refused(key, make, want):
         with pytest.raises(ipv.IpvError) as e:
             call(b)
         assert e.value.status == want, call.__name__
+
+
+def test_grid_sizes_are_taken_as_a_fresh_shape_takes_them():
+    """Also after a call with the same grid has been seen: floats refused, anything with an index accepted, by its value now."""
+    b = bufs()
+    run = lambda gh: ipv.ipv_compress(b["K"], b["V"], b["fr"], b["pa"], S, C, 0.5, 1, None, b["tar"], b["van"],  # noqa: E731
+                                      b["keep"], b["ws"], gh, GW)
+    run(GH)
+    with pytest.raises(TypeError):
+        run(float(GH))
+    run(np.array(GH))
+    changing = torch.tensor(GH)
+    run(changing)
+    changing.fill_(0)
+    with pytest.raises(ipv.IpvError) as e:
+        run(changing)
+    assert e.value.status == ipv.ERR_SHAPE
 
 
 def test_calls_follow_the_current_stream():
