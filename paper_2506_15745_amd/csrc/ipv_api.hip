@@ -574,18 +574,27 @@ ipv_status stretch_gather(const Dims& d, void* K, void* V, const Stretch& sr, co
 // ------------------------------------------------------------ small slices (ipv_small.hpp)
 // Whether a pass over slices of at most n rows goes out as one launch, a
 // workgroup per slice: the plain scores (pooling and the other modes couple a
-// layer's slices or have steps of their own), slices that run all at once, and
-// 256 rows and 64 KB of keys at most. Passes as GPU time alone, four launches
+// layer's slices or have steps of their own), slices that run all at once,
+// 256 rows and 64 KB of keys at most, and 24 or 32 KB of keys in a frame of the grid. Passes as GPU time alone, four launches
 // against one (a graph of ten): 128 rows of 256 bytes 15.3 -> 13.3 us (2 slices),
 // 23.9 -> 16.3 (256 slices); 256 rows 18.4 -> 16.4, 32.6 -> 22.2. Beyond, the one
 // workgroup's share of the bandwidth counts: 512 rows of 256 bytes 17.8 -> 20.1,
 // of 64 bytes 16.5 -> 19.0, 512 slices of 64 bytes 42.8 -> 45.2. A caller that is
 // bound by its launches gains more (two passes and a gather of 128 rows: 7
 // launches -> 2, 38 -> 28 us a call).
-constexpr int64_t kSmallBytes = 64 << 10;
-bool small_pass(const Dims& d, int32_t n, int32_t r, uint32_t mode, const double* cv_tau) {
+// The recent-key table takes the workgroup a round (with its own scan of the
+// window) for every 16 KB of key rows of one frame, and the tiles go over every
+// position of the grid, so the grid has to be small too. 256 rows of 256 bytes,
+// 2 slices, the same measure with the metadata restored each time: 64 positions (a
+// round) 20.0 -> 17.1, 81 (20 KB) 20.7 -> 19.8, 117 (29 KB) 20.6 -> 21.0; 64 rows of
+// 1024 bytes: 24 positions (24 KB) 20.6 -> 20.0, 30 20.5 -> 20.7; single calls on
+// 144 positions 25 -> 28, on 576 24 -> 49, 64 rows of 1024 bytes on 4096 29 -> 884.
+// A call over a stretch is bound by its launches sooner and takes 32 KB (12 passes
+// of 250 rows on 128 positions 237 -> 222 us, 10 of 64 rows on 30 194 -> 174).
+constexpr int64_t kSmallBytes = 64 << 10, kSmallFrame = 24 << 10, kSmallFrameStretch = 32 << 10;
+bool small_pass(const Dims& d, int32_t n, int32_t r, uint32_t mode, const double* cv_tau, int64_t frame = kSmallFrame) {
   return !cv_tau && (mode & ~(uint32_t)(IPV_TAR_REVERSE | IPV_VAN_REVERSE)) == 0 && n <= kSmallRows && r <= 32 &&
-         d.slices <= kComputeUnits && (int64_t)n * d.D * d.elem <= kSmallBytes;
+         d.slices <= kComputeUnits && n * d.D * d.elem <= kSmallBytes && d.p * d.D * d.elem <= frame;
 }
 
 template <typename T, int D, class ST>
@@ -1063,7 +1072,7 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
       };
       const Stretch sr = stretch(l.n0, l.pending, l.pending ? keep : nullptr);
       int32_t* places = reinterpret_cast<int32_t*>(ws_table(ws));
-      const bool small = small_pass(s, n, r, mode, cv_tau);
+      const bool small = small_pass(s, n, r, mode, cv_tau, kSmallFrameStretch);
       const int32_t new_frames = (int32_t)fires_in(budget), n_next = budget + new_frames * rows;  // the next pass's
       if (!uniform && !small)
         IPV_TRY(stretch_scores(s, k, v, sr, fr, pa, n, r, tr, vn, ws, st, chunks, adjacent,
@@ -1080,7 +1089,7 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
         IPV_TRY(run_small_stretch(s, k, v, sr, fr, pa, n, budget, floor_share(alpha, budget), r, mode, tr, vn,
                                   l.pending > 0 ? sr.n0 : 0u, em, last, ws, st));
       else if (s.B == d.B && !last && !uniform && !pool && l.n0 <= budget && ahead_fits(s, n, mode) &&
-               !small_pass(s, n_next, r, mode, cv_tau)) {  // the whole batch: it stays alike, so the next pass is its
+               !small_pass(s, n_next, r, mode, cv_tau, kSmallFrameStretch)) {  // the whole batch: it stays alike, so the next pass is its
         const bool then_last = l.left == 2;
         ahead.norms = true;
         ahead.table = !adjacent && new_frames > r;

@@ -1,7 +1,7 @@
 """Passes of small slices, which go out as one launch, against the step entry
 points (launches of their own), bit for bit: the edges of the rule (256 and
-257 rows, 64 KB of keys and just beyond, 256 and 257 slices), every row size,
-one row, ragged batches, a window of the whole cache, reversed stages."""
+257 rows, 64 KB of keys and just beyond, 256 and 257 slices, frames of 24 KB and
+beyond, windows of 32 and 33 frames), every row size, one row, ragged batches, a window of the whole cache, reversed stages."""
 import numpy as np
 import pytest
 import torch
@@ -24,7 +24,12 @@ CASES = {
     "whole-window": ((120,), 2, 2, 256, (3, 5), 120, 8, 120, "bf16", ipv.TAR_REVERSE),
     "wide-rows": ((64,), 1, 3, 256, (2, 3), 32, 3, 67, "f32", ipv.VAN_REVERSE),
     "long-window": ((250,), 1, 2, 32, (1, 5), 200, 33, 250, "bf16", 0),
+    # the most LDS that the rule admits: 256 positions a round, 32 frames a position
+    "most-lds": ((250,), 1, 2, 32, (1, 5), 200, 32, 250, "bf16", 0),
+    "24KB-frames": ((256,), 1, 2, 64, (8, 12), 200, 1, 256, "f32", 0),
+    "beyond-24KB-frames": ((256,), 1, 2, 64, (1, 97), 200, 1, 256, "f32", 0),
     "ragged": ((90, 0, 250, 131, 90), 2, 2, 64, (6, 7), 88, 2, 251, "bf16", ipv.TAR_REVERSE | ipv.VAN_REVERSE),
+    "two-table-rounds": ((240,), 1, 2, 32, (10, 15), 239, 1, 240, "f32", ipv.TAR_REVERSE),
     "wide-grid": ((240,), 1, 2, 32, (8, 15), 239, 1, 240, "f32", 0),
 }
 

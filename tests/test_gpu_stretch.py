@@ -48,6 +48,11 @@ CASES = {
     "ahead-rows-above-the-budget": (1, 2, 128, (7, 7), 49, (900,), 80, 1000, 500, 2, 1049, "bf16", 0, None),
     # the first pass has 260 rows, the later ones 250 and go out as one launch each
     "ahead-then-small": (1, 2, 64, (4, 5), 20, (0,), 40, 250, 230, 2, 270, "bf16", 0, None),
+    # passes of one launch each: the most LDS that its rule admits, windows scanned; two rounds of the table
+    "small-most-lds": (1, 2, 32, (1, 5), 5, (0, 100), 60, 240, 190, 32, 250, "bf16", 0, None),
+    "small-32KB-frames": (1, 2, 128, (8, 16), 40, (0, 60), 30, 200, 150, 1, 250, "bf16", 0, None),
+    "beyond-32KB-frames": (1, 2, 128, (3, 43), 40, (0, 60), 30, 200, 150, 1, 250, "bf16", 0, None),
+    "small-two-table-rounds": (1, 2, 128, (9, 9), 40, (0, 33), 30, 200, 150, 1, 250, "bf16", ipv.VAN_REVERSE, None),
     "ahead-adjacent": (2, 2, 256, (9, 13), 117, (0,), 60, 1700, 800, 3, 1819, "f32", ipv.TAR_ADJACENT, None),
     "ahead-adjacent-shared": (3, 2, 64, (9, 13), 117, (0, 0), 60, 1700, 1500, 4, 1817, "bf16",
                         ipv.TAR_ADJACENT | ipv.HEAD_SHARED, None),

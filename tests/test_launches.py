@@ -1,8 +1,10 @@
 """What calls launch, on a host-only build that writes the launches down."""
+import ctypes
+
 import pytest
 
 from paper_2506_15745_amd import ipv
-from tests.recorder import Stream, recorder, recorder_library  # noqa: F401
+from tests.recorder import BASE, Stream, recorder, recorder_library  # noqa: F401
 
 # 16 streams below the cap at counts of their own, all at it within the first frame
 FIRE_TOGETHER = dict(L=2, H=2, D=64, grid=(14, 14), cap=6272, budget=3136, r=4, entry=[6076 + b for b in range(16)])
@@ -21,3 +23,34 @@ def test_streams_alike_after_a_pass_share_its_launches(recorder, mode, tau, chai
     got = recorder.launches()
     assert len(got) <= 16 * chain + (passes - 1) * chain + 1
     assert [x.kernel for x in got].count("k_stretch_gather") == 1
+
+
+def compress_kernels(recorder, n, L, H, D, grid, r, dtype):  # noqa: F811
+    """The kernels of one ipv_compress of n rows a slice."""
+    s = ipv.Shape(1, L, H, D, n, *grid, dtype)
+    a = {k: BASE * (i + 1) for i, k in enumerate("K V fr pa tar van keep ws".split())}
+    recorder.start()
+    assert ipv.lib().ipv_compress(ctypes.byref(s), a["K"], a["V"], a["fr"], a["pa"], (ctypes.c_int32 * 1)(n), n // 2, 0.5, r, 0,
+                                  None, a["tar"], a["van"], a["keep"], a["ws"], ipv.workspace_bytes(s), None) == ipv.OK
+    return recorder.launches()
+
+
+@pytest.mark.parametrize("n,D,dtype,grid,one", [
+    (256, 128, ipv.BF16, (8, 8), True), (256, 128, ipv.BF16, (8, 12), True), (256, 128, ipv.BF16, (1, 97), False),
+    (256, 128, ipv.BF16, (24, 24), False), (64, 256, ipv.F32, (4, 6), True), (64, 256, ipv.F32, (5, 5), False),
+    (64, 256, ipv.F32, (64, 64), False), (256, 32, ipv.BF16, (16, 24), True), (256, 32, ipv.BF16, (90, 90), False)])
+def test_a_wide_grid_has_the_launches_of_large_slices(recorder, n, D, dtype, grid, one):  # noqa: F811
+    """In one workgroup the recent-key table and the tiles take rounds in proportion to the grid."""
+    kernels = [x.kernel for x in compress_kernels(recorder, n, 1, 2, D, grid, 1, dtype)]
+    assert kernels == (["k_small_pass"] if one else ["k_table_van", "k_score_sweep", "k_select", "k_compact"])
+
+
+def test_a_small_pass_fits_the_lds(recorder):  # noqa: F811
+    """The dynamic part of the largest request; the static part (the selection's, and the places of a
+    stretch) is below 64 KB, and a CU has 160 KB."""
+    most = 0
+    for D, dtype in ((32, ipv.BF16), (64, ipv.BF16), (32, ipv.F32), (256, ipv.BF16), (256, ipv.F32)):
+        for x in compress_kernels(recorder, 64, 1, 2, D, (1, 2), 32, dtype):
+            assert x.kernel == "k_small_pass"
+            most = max(most, x.lds)
+    assert most == 32 << 10
