@@ -313,7 +313,8 @@ ipv_status ipv_ckv_step(const ipv_shape* shape, void* K, void* V, int32_t* frame
  * they lie: between two passes of a stream only its metadata is compacted, and
  * its surviving rows are written into K and V once, after its last pass of the
  * call (the result is that of one append per frame and one compaction per
- * pass); the frames after that are appended. frames_K / frames_V must not
+ * pass); the frames after that are appended. (A stream's only pass of a call,
+ * if few of its rows are new, appends them and runs in the cache.) frames_K / frames_V must not
  * overlap K / V.
  * Every step is checked before the first is enqueued (the counts of the
  * whole stretch follow from the counts, rows, mem_cap and budget), so a

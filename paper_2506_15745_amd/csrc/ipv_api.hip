@@ -1007,14 +1007,30 @@ ipv_status scratch_of(hipStream_t st, void** out) {
   return IPV_OK;
 }
 
+// Whether a call's only pass of a stream runs in the cache, after an append of its
+// new rows, instead of over the frames where they lie. That costs the append's read
+// and write of the new rows and saves the TaR tiles over old rows, which fetch an m
+// vector for every row; so it wins while few of the rows are new, and with pooling
+// (the norms are read three more times) up to a little more. 112 slices of 6272 rows,
+// 1 new frame of 32: 182 us over the frames, 167 in the cache; 3: 181, 170; 4: 179,
+// 175; 6: 178, 183; 12288 rows, 1 of 48: 311, 286; 4: 308, 300; 5: 307, 304; 6: 307,
+// 315, with pooling 351, 343; 80 slices of 32768 rows, 1 of 167: 586, 540; 12: 578,
+// 572; 16: 579, 586. The consecutive-frame mode and Uniform Select have no m vectors:
+// 165 and 165 (1 frame of 32), 94 and 94.
+bool pass_in_cache(int32_t n0, int32_t n, uint32_t mode, bool pool) {
+  if (mode & (IPV_TAR_ADJACENT | IPV_UNIFORM_SELECT)) return false;
+  return (int64_t)(n - n0) * (pool ? 8 : 10) <= n;
+}
+
 // Frames [0, n_frames) of a call of the continual-compression loop whose
 // arguments are checked: the passes run over the frames where they lie, one
 // gather per stream follows its last pass, and the frames after that are
-// appended. The places of a stream's rows between two passes are kept in its
-// rows of keep_idx, its value norms in van (without pooling, which overwrites
-// them); the last pass leaves its keep set and scores there, and the places of
-// the rows that stay in the workspace's table region, whose contents (the m
-// vectors or prev rows) the pass has used by then.
+// appended (a stream's only pass may run in the cache: pass_in_cache). The places
+// of a stream's rows between two passes are kept in its rows of keep_idx, its
+// value norms in van (without pooling, which overwrites them); the last pass
+// leaves its keep set and scores there, and the places of the rows that stay in
+// the workspace's table region, whose contents (the m vectors or prev rows) the
+// pass has used by then.
 ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int32_t* patch_idx, int32_t* n_tokens,
                        const char* fk, const char* fv, int32_t n_frames, int32_t rows, int32_t first_frame_id,
                        int32_t mem_cap, int32_t budget, double alpha, int32_t r, uint32_t mode, const double* cv_tau,
@@ -1034,6 +1050,12 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
       if (later < 1) break;
     }
   }
+  auto done = [&](int64_t b, int64_t e, int64_t f) {  // streams [b, e) had a pass at frame f
+    for (; b < e; ++b) {
+      ls[b] = {budget, (int32_t)f + 1, ls[b].left - 1};
+      ++passes[b];
+    }
+  };
   AheadDone ahead;
   for (;;) {
     // the next frame at which a stream reaches the cap (frames [pending, f] are its new rows)
@@ -1055,6 +1077,14 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
       int32_t* keep = keep_idx + b0 * ks;
       float* tr = at_stream(tar, b0, rs);
       float* vn = at_stream(van, b0, rs);
+      const bool small = small_pass(s, n, r, mode, cv_tau, kSmallFrameStretch);
+      if (last && l.pending == 0 && !small && pass_in_cache(l.n0, n, mode, pool)) {
+        IPV_TRY(append_run(d, b0, e, K, V, frame_idx, patch_idx, l.n0, fk, fv, rows, (int32_t)f + 1, frame_bytes,
+                           first_frame_id, 0, st));
+        IPV_TRY(compress_run(s, k, v, fr, pa, n, Whole{}, budget, alpha, r, mode, cv_tau, tr, vn, keep, ws, st, nullptr));
+        done(b0, e, f);
+        return IPV_OK;
+      }
       // the pass over l_n0 rows and the frames from `pending` on
       auto stretch = [&](int32_t l_n0, int32_t pending, const int32_t* src) {
         Stretch sr{};
@@ -1072,7 +1102,6 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
       };
       const Stretch sr = stretch(l.n0, l.pending, l.pending ? keep : nullptr);
       int32_t* places = reinterpret_cast<int32_t*>(ws_table(ws));
-      const bool small = small_pass(s, n, r, mode, cv_tau, kSmallFrameStretch);
       const int32_t new_frames = (int32_t)fires_in(budget), n_next = budget + new_frames * rows;  // the next pass's
       if (!uniform && !small)
         IPV_TRY(stretch_scores(s, k, v, sr, fr, pa, n, r, tr, vn, ws, st, chunks, adjacent,
@@ -1103,10 +1132,7 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
       // only the gather asks how many rows the streams entered the call with: the most of them bounds its waits
       const int32_t n_entry = *std::max_element(n_tokens + b0, n_tokens + e);
       if (last && !small) IPV_TRY(stretch_gather(s, k, v, sr, places, n_entry, budget, ws, st));
-      for (int64_t b = b0; b < e; ++b) {
-        ls[b] = {budget, (int32_t)f + 1, l.left - 1};
-        ++passes[b];
-      }
+      done(b0, e, f);
       return IPV_OK;
     }));
   }

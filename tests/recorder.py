@@ -34,7 +34,8 @@ class Recorder:
         for i in range(self.lib.rec_count()):
             dims = (ctypes.c_uint * 4)()
             name = self.lib.rec_launch(i, ctypes.byref(dims)).decode()
-            length, kernel = re.search(r"(\d\d?)(k_\w+)", name).groups()  # mangled: the name's length, then the name
+            # mangled: the namespace, the name's length, the name
+            length, kernel = re.search(r"(\d\d?)(k_\w+)", name.replace("12_GLOBAL__N_1", "")).groups()
             out.append(Launch(kernel[:int(length)], *dims))
         return out
 

@@ -53,6 +53,9 @@ CASES = {
     "small-32KB-frames": (1, 2, 128, (8, 16), 40, (0, 60), 30, 200, 150, 1, 250, "bf16", 0, None),
     "beyond-32KB-frames": (1, 2, 128, (3, 43), 40, (0, 60), 30, 200, 150, 1, 250, "bf16", 0, None),
     "small-two-table-rounds": (1, 2, 128, (9, 9), 40, (0, 33), 30, 200, 150, 1, 250, "bf16", ipv.VAN_REVERSE, None),
+    # one pass with few new rows in a call, then frames without one
+    "in-cache": (2, 2, 128, (7, 7), 49, (1990, 1960, 1960), 6, 2000, 1600, 4, 2051, "bf16", ipv.HEAD_SHARED, None),
+    "in-cache-pooled": (4, 1, 64, (7, 7), 30, (1990, 0, 1870), 8, 2000, 1600, 4, 2030, "f32", 0, (0.3, 0.5, 0.7)),
     "ahead-adjacent": (2, 2, 256, (9, 13), 117, (0,), 60, 1700, 800, 3, 1819, "f32", ipv.TAR_ADJACENT, None),
     "ahead-adjacent-shared": (3, 2, 64, (9, 13), 117, (0, 0), 60, 1700, 1500, 4, 1817, "bf16",
                         ipv.TAR_ADJACENT | ipv.HEAD_SHARED, None),

@@ -25,6 +25,19 @@ def test_streams_alike_after_a_pass_share_its_launches(recorder, mode, tau, chai
     assert [x.kernel for x in got].count("k_stretch_gather") == 1
 
 
+@pytest.mark.parametrize("frames,mode,tau,where", [
+    (3, 0, None, "cache"), (4, 0, None, "frames"), (3, ipv.HEAD_SHARED, None, "cache"), (4, 0, (0.3, 0.5, 0.7), "cache"),
+    (5, 0, (0.3, 0.5, 0.7), "frames"), (1, ipv.TAR_ADJACENT, None, "frames"), (1, ipv.UNIFORM_SELECT, None, "frames")])
+def test_a_pass_with_few_new_rows_runs_in_the_cache(recorder, frames, mode, tau, where):  # noqa: F811
+    s = Stream(L=28, H=4, D=128, grid=(14, 14), cap=6272, budget=3136, r=4, entry=[6272 - 196 * frames])
+    recorder.start()
+    rc, n, ps = s.call(frames, mode, tau)
+    assert rc == ipv.OK and ps == [1] and n == [3136]
+    kernels = recorder.kernels()
+    assert ("k_append" in kernels and "k_compact" in kernels) == (where == "cache")
+    assert ("k_stretch_gather" in kernels) == (where == "frames")
+
+
 def compress_kernels(recorder, n, L, H, D, grid, r, dtype):  # noqa: F811
     """The kernels of one ipv_compress of n rows a slice."""
     s = ipv.Shape(1, L, H, D, n, *grid, dtype)
