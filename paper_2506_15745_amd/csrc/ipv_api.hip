@@ -1146,6 +1146,11 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
   return IPV_OK;
 }
 
+bool overlap(const void* a, int64_t a_bytes, const void* b, int64_t b_bytes) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + (uintptr_t)b_bytes && y < x + (uintptr_t)a_bytes;
+}
+
 __global__ void k_copy_word(uint32_t* dst, const uint32_t* src) {
   if (threadIdx.x == 0) *dst = *src;
 }
@@ -1299,15 +1304,32 @@ ipv_status ipv_ckv_stream(const ipv_shape* shape, void* K, void* V, int32_t* fra
     IPV_TRY(check_ws(d, ws, ws_bytes));
   }
   for (int64_t b = 0; b < d.B; ++b) passes[b] = 0;
+  const int64_t frame_bytes = d.slices * rows * d.D * d.elem, cache_bytes = d.B * kv_bytes_per_stream(d);
+  const int64_t call_bytes = n_frames * frame_bytes;
+  const char* fk = static_cast<const char*>(frames_K);
+  const char* fv = static_cast<const char*>(frames_V);
+  if (overlap(fk, call_bytes, K, cache_bytes) || overlap(fk, call_bytes, V, cache_bytes) ||
+      overlap(fv, call_bytes, K, cache_bytes) || overlap(fv, call_bytes, V, cache_bytes)) {
+    // frames in the cache's own memory (written where they will be appended, say) do not stay
+    // where they are while passes run: the loop step by step
+    for (int32_t f = 0; f < n_frames; ++f) {
+      IPV_TRY(ipv_ckv_step(shape, K, V, frame_idx, patch_idx, n_tokens, fk + f * frame_bytes, fv + f * frame_bytes, rows,
+                           first_frame_id + f, 0, mem_cap, budget, alpha, recent_frames, mode, cv_tau, tar, van,
+                           keep_idx, ws, ws_bytes, after.data(), pass.data(), stream));
+      for (int64_t b = 0; b < d.B; ++b) {
+        n_tokens[b] = after[b];
+        passes[b] += pass[b];
+      }
+    }
+    return IPV_OK;
+  }
   // places of frame rows are 31-bit: longer calls are taken in parts
   const int32_t part = std::max<int32_t>(1, (INT32_MAX - 1) / rows);
-  const int64_t frame_bytes = d.slices * rows * d.D * d.elem;
   for (int32_t f = 0; f < n_frames; f += std::min(part, n_frames - f)) {
     const int32_t count = std::min(part, n_frames - f);
-    IPV_TRY(stream_part(d, K, V, frame_idx, patch_idx, n_tokens, static_cast<const char*>(frames_K) + f * frame_bytes,
-                        static_cast<const char*>(frames_V) + f * frame_bytes, count, rows, first_frame_id + f, mem_cap,
-                        budget, alpha, recent_frames, mode, cv_tau, tar, van, keep_idx, ws, passes,
-                        static_cast<hipStream_t>(stream)));
+    IPV_TRY(stream_part(d, K, V, frame_idx, patch_idx, n_tokens, fk + f * frame_bytes, fv + f * frame_bytes, count, rows,
+                        first_frame_id + f, mem_cap, budget, alpha, recent_frames, mode, cv_tau, tar, van, keep_idx, ws,
+                        passes, static_cast<hipStream_t>(stream)));
   }
   return IPV_OK;
 }

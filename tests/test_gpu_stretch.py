@@ -124,3 +124,25 @@ def test_stream_passes_equal_step_by_step(name, cut):
                 for x, y in ((c1.tar, c2.tar), (c1.van, c2.van)):
                     assert torch.equal(x[b, :, :, :at[b]].view(torch.int32), y[b, :, :, :at[b]].view(torch.int32))
     print(name, "passes", passes1, "rows", n1, flush=True)
+
+
+def test_frames_in_the_caches_own_rows():
+    """A program that writes frames where they will be appended: the same as with the frames in a buffer of their own."""
+    gh = gw = 7
+    p, D, n0, frames, cap, budget, r = 49, 64, 98, 39, 2000, 1000, 4
+    S = n0 + frames * p
+    st = synth.fresh_cache(77, 1, 1, S, D, gh, gw, S, synth.F32, synth.RhoSpec(0.0, 0.95), (0.5,))
+    out = []
+    for own in (False, True):
+        K, V, fr, pa = (P.to_device(np.ascontiguousarray(getattr(st, a)[None])) for a in ("K", "V", "frame_idx", "patch_idx"))
+        fK, fV = (t[0, 0, 0, n0:].view(frames, 1, 1, 1, p, D) for t in (K, V))
+        if own:
+            fK, fV = fK.clone(), fV.clone()
+        c = ipv.Compressor(K, gh, gw, budget)
+        n, passes = ipv.ipv_ckv_stream(K, V, fr, pa, n0, fK, fV, 2, cap, budget, 0.5, r, None, c.tar, c.van, c.keep_idx,
+                                       c.ws, gh, gw)
+        torch.cuda.synchronize()
+        assert passes == 1 and c.device_errors() == 0
+        out.append([t[..., :n, :] for t in (K, V)] + [t[..., :n] for t in (fr, pa)] + [c.keep_idx])
+    for x, y in zip(*out):
+        assert torch.equal(x, y)

@@ -38,6 +38,21 @@ def test_a_pass_with_few_new_rows_runs_in_the_cache(recorder, frames, mode, tau,
     assert ("k_stretch_gather" in kernels) == (where == "frames")
 
 
+@pytest.mark.parametrize("frames_at,cache,apart", [
+    ("fK", "K", False), ("fV", "V", False), ("fK", "V", False), ("fV", "K", False), ("fK", "K", True), ("fV", "V", True)])
+def test_frames_in_the_caches_memory_go_frame_by_frame(recorder, frames_at, cache, apart):  # noqa: F811
+    """Passes over frames where they lie would read what the gather has overwritten."""
+    s = Stream(L=1, H=1, D=64, grid=(14, 14), cap=6272, budget=3136, r=4, entry=[196])
+    # the frames begin in the cache's last row, or where the cache ends
+    s.at[frames_at] = s.at[cache] + (s.shape.capacity - (0 if apart else 1)) * 64 * 2
+    recorder.start()
+    rc, n, ps = s.call(64)
+    assert rc == ipv.OK and ps == [3] and n == [3136 + 196]
+    kernels = recorder.kernels()
+    assert any("stretch" in k for k in kernels) == apart
+    assert kernels.count("k_append") == (1 if apart else 64)
+
+
 def compress_kernels(recorder, n, L, H, D, grid, r, dtype):  # noqa: F811
     """The kernels of one ipv_compress of n rows a slice."""
     s = ipv.Shape(1, L, H, D, n, *grid, dtype)
