@@ -320,11 +320,11 @@ ipv_status ipv_ckv_step(const ipv_shape* shape, void* K, void* V, int32_t* frame
  * Every step is checked before the first is enqueued (the counts of the
  * whole stretch follow from the counts, rows, mem_cap and budget), so a
  * rejected call enqueues nothing. The only error that can come after the
- * first launch is IPV_ERR_HIP (the runtime refused a launch or a copy): the
- * caches' contents are then unspecified and n_tokens holds the counts it came
- * with. The work
- * of all frames shares tar, van, keep_idx and the workspace, which hold the
- * last pass's values on return. Problems only the device sees (IPV_DEV_* bits)
+ * first launch is IPV_ERR_HIP (the runtime refused a launch): the caches' rows
+ * and metadata are then unspecified from the first launch on, n_tokens holds the
+ * counts it came with and passes zeros. The work of all frames
+ * shares tar, van, keep_idx and the workspace, which hold the last pass's values
+ * on return. Problems only the device sees (IPV_DEV_* bits)
  * accumulate in the workspace's error word over all passes of the call and do
  * not stop it: read the word with ipv_read_device_errors after the call.
  */

@@ -1303,7 +1303,10 @@ ipv_status ipv_ckv_stream(const ipv_shape* shape, void* K, void* V, int32_t* fra
     if (!aligned(tar, 16) || !aligned(van, 16) || !aligned(keep_idx, 16)) return IPV_ERR_ALIGN;
     IPV_TRY(check_ws(d, ws, ws_bytes));
   }
+  // a call that the runtime stops halfway reports the counts it came with and no passes
   for (int64_t b = 0; b < d.B; ++b) passes[b] = 0;
+  std::vector<int32_t> done((size_t)d.B, 0);
+  n.assign(n_tokens, n_tokens + d.B);
   const int64_t frame_bytes = d.slices * rows * d.D * d.elem, cache_bytes = d.B * kv_bytes_per_stream(d);
   const int64_t call_bytes = n_frames * frame_bytes;
   const char* fk = static_cast<const char*>(frames_K);
@@ -1313,24 +1316,26 @@ ipv_status ipv_ckv_stream(const ipv_shape* shape, void* K, void* V, int32_t* fra
     // frames in the cache's own memory (written where they will be appended, say) do not stay
     // where they are while passes run: the loop step by step
     for (int32_t f = 0; f < n_frames; ++f) {
-      IPV_TRY(ipv_ckv_step(shape, K, V, frame_idx, patch_idx, n_tokens, fk + f * frame_bytes, fv + f * frame_bytes, rows,
+      IPV_TRY(ipv_ckv_step(shape, K, V, frame_idx, patch_idx, n.data(), fk + f * frame_bytes, fv + f * frame_bytes, rows,
                            first_frame_id + f, 0, mem_cap, budget, alpha, recent_frames, mode, cv_tau, tar, van,
                            keep_idx, ws, ws_bytes, after.data(), pass.data(), stream));
       for (int64_t b = 0; b < d.B; ++b) {
-        n_tokens[b] = after[b];
-        passes[b] += pass[b];
+        n[b] = after[b];
+        done[b] += pass[b];
       }
     }
-    return IPV_OK;
+  } else {
+    // places of frame rows are 31-bit: longer calls are taken in parts
+    const int32_t part = std::max<int32_t>(1, (INT32_MAX - 1) / rows);
+    for (int32_t f = 0; f < n_frames; f += std::min(part, n_frames - f)) {
+      const int32_t count = std::min(part, n_frames - f);
+      IPV_TRY(stream_part(d, K, V, frame_idx, patch_idx, n.data(), fk + f * frame_bytes, fv + f * frame_bytes, count, rows,
+                          first_frame_id + f, mem_cap, budget, alpha, recent_frames, mode, cv_tau, tar, van, keep_idx, ws,
+                          done.data(), static_cast<hipStream_t>(stream)));
+    }
   }
-  // places of frame rows are 31-bit: longer calls are taken in parts
-  const int32_t part = std::max<int32_t>(1, (INT32_MAX - 1) / rows);
-  for (int32_t f = 0; f < n_frames; f += std::min(part, n_frames - f)) {
-    const int32_t count = std::min(part, n_frames - f);
-    IPV_TRY(stream_part(d, K, V, frame_idx, patch_idx, n_tokens, fk + f * frame_bytes, fv + f * frame_bytes, count, rows,
-                        first_frame_id + f, mem_cap, budget, alpha, recent_frames, mode, cv_tau, tar, van, keep_idx, ws,
-                        passes, static_cast<hipStream_t>(stream)));
-  }
+  std::copy(n.begin(), n.end(), n_tokens);
+  std::copy(done.begin(), done.end(), passes);
   return IPV_OK;
 }
 

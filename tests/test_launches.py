@@ -53,6 +53,21 @@ def test_frames_in_the_caches_memory_go_frame_by_frame(recorder, frames_at, cach
     assert kernels.count("k_append") == (1 if apart else 64)
 
 
+@pytest.mark.parametrize("own_memory", [True, False])
+def test_a_call_that_the_runtime_stops_reports_what_it_came_with(recorder, own_memory):  # noqa: F811
+    s = Stream(L=1, H=1, D=64, grid=(14, 14), cap=6272, budget=3136, r=4, entry=[196, 3136, 0])
+    if not own_memory:
+        s.at["fK"] = s.at["K"]
+    recorder.start()
+    assert s.call(40)[0] == ipv.OK
+    total = len(recorder.launches())
+    assert total > 10
+    for stop in range(total):
+        recorder.start(fail=stop)
+        assert s.call(40) == (ipv.ERR_HIP, [196, 3136, 0], [0, 0, 0])
+        assert len(recorder.launches()) == stop  # nothing is launched after the refusal
+
+
 def compress_kernels(recorder, n, L, H, D, grid, r, dtype):  # noqa: F811
     """The kernels of one ipv_compress of n rows a slice."""
     s = ipv.Shape(1, L, H, D, n, *grid, dtype)
