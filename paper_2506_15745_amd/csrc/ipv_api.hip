@@ -452,7 +452,7 @@ ipv_status stretch_scores_t(const Dims& d, const char* K, const char* V, const S
   const uint32_t rows = sr.rows.d, new_frames = ((uint32_t)n - sr.n0) / rows;
   const uint32_t old_tiles = (sr.n0 + TILE - 1) / TILE, cols = (rows + C::GROUPS - 1) / C::GROUPS;
   const uint32_t tiles = old_tiles + (new_frames + C::U - 1) / C::U * cols;
-  const uint32_t group = sr.n0 == 0 ? kSliceGroup : 0u;
+  const uint32_t group = sr.n0 == 0 ? slice_group(slices, (uint32_t)(d.p * d.D) * 4u) : 0u;
   const uint32_t work = ((slices + (1u << group) - 1) >> group << group) * tiles;
   const uint32_t cv = cv_tau ? (uint32_t)(d.B * d.L) : 0u;
   const int32_t sure_past = (int32_t)std::max<int64_t>(0, (int64_t)n - (int64_t)r * d.p);

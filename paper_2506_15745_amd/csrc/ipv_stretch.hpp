@@ -213,7 +213,7 @@ __global__ __launch_bounds__(256) void k_stretch_table_van(const char* __restric
   const uint32_t logical = xcd_logical_id(blockIdx.x - table_padded, tile_blocks);
   if (logical >= n_work) return;
   uint32_t slice, t;
-  if (v0 >= st.n0) {  // frames only: neighbouring slices in turn (72B-class cache 986 -> 965 us)
+  if (v0 >= st.n0) {  // frames only: neighbouring slices in turn (640 slices of 12288 rows 1514 -> 1481 us a call)
     t = fast_div(logical, vslices);
     slice = logical - t * vslices.d;
   } else {
@@ -333,12 +333,26 @@ __device__ __forceinline__ void stretch_tar_new(const Stretch& st, int64_t S, ui
 
 // Frames of all slices lie one after another, so tiles that run together read
 // nearby memory when neighbouring slices take the same tile in turn. The TaR
-// tiles of a pass without old rows go 8 slices at a time, whose m tables (100 KB
-// each for a 14x14 grid and 128 elements) fit an XCD's 4 MB of L2: 973 -> 933 us on
-// the 72B-class cache (16 at a time 978 us). Old rows are strewn over their
-// slice's table, and only that one stays in L2 with them: one slice at a time
-// (75 us a pass of the 16x16 video, 78 us with 8 in turn).
-constexpr uint32_t kSliceGroup = 3;  // log2
+// tiles of a pass without old rows go 1, 2, 4 or 8 slices at a time (log2 here): as
+// many as have m tables of 1.2 MB together (an XCD's L2 holds 4 MB and the keys
+// stream through it), and 7 groups to an XCD at least (an XCD takes a run of slices,
+// and the groups that two of them share have their tables in both). A call with one
+// pass and its gather, us, 1 / 2 / 4 / 8 / 16 slices at a time:
+//   112 slices, tables of 100 KB   171 / 168 / 169 / 173 / 172
+//   640 slices                    4081 / 4062 / 4039 / 4029 / 4079
+//   112 slices, 131 KB             291 / 287 / 292 / 300 / 296
+//   640 slices                    1518 / 1500 / 1490 / 1479 / 1506
+//   640 slices, 295 KB            2363 / 2357 / 2356 / 2376 / 2406
+//   112 slices, 590 KB             415 / 416 / 421 / 431 / 435
+//   320 slices                    2290 / 2291 / 2307 / 2371 / 2376
+//   224 slices, 25 KB              583 / 586 / 568 / 563 / 568
+// Old rows are strewn over their slice's table, and only that one stays in L2 with
+// them: one slice at a time (75 us a pass of the 16x16 video, 78 us with 8 in turn).
+inline uint32_t slice_group(uint32_t slices, uint32_t table_bytes) {
+  uint32_t g = 0;
+  while (g < 3 && slices / 56u >= 2u << g && (2u << g) * (uint64_t)table_bytes <= 1200000u) ++g;
+  return g;
+}
 
 // The TaR launch of a pass, with the pooling CV blocks first (cv_padded = 0:
 // none). tiles: tiles per slice, the first old_tiles of them over the old rows.

@@ -44,6 +44,9 @@ CASES = {
     "ahead-window-is-the-new-frames": (2, 2, 256, (5, 5), 25, (0,), 60, 500, 400, 4, 525, "bf16", 0, None),
     "ahead-192-selections": (96, 2, 32, (6, 7), 42, (0,), 40, 600, 300, 2, 642, "bf16", 0, None),
     "ahead-193-selections": (193, 1, 32, (6, 7), 42, (0,), 40, 600, 300, 2, 642, "bf16", 0, None),
+    # TaR tiles of frames, 4 and 8 slices in turn, slices left over
+    "4-slices-in-turn": (113, 2, 32, (5, 5), 25, (0,), 24, 300, 200, 2, 325, "bf16", 0, None),
+    "8-slices-in-turn": (449, 1, 32, (5, 5), 25, (0,), 24, 300, 200, 2, 325, "bf16", 0, None),
     "ahead-narrow-frames": (1, 2, 64, (8, 8), 41, (20, 20), 60, 900, 400, 2, 943, "f32", ipv.VAN_REVERSE, None),
     "ahead-rows-above-the-budget": (1, 2, 128, (7, 7), 49, (900,), 80, 1000, 500, 2, 1049, "bf16", 0, None),
     # the first pass has 260 rows, the later ones 250 and go out as one launch each

@@ -68,6 +68,20 @@ def test_a_call_that_the_runtime_stops_reports_what_it_came_with(recorder, own_m
         assert len(recorder.launches()) == stop  # nothing is launched after the refusal
 
 
+@pytest.mark.parametrize("slices,D,grid,padded", [
+    (57, 128, (14, 14), 57), (113, 128, (14, 14), 114), (225, 128, (14, 14), 228), (449, 128, (14, 14), 456),
+    (113, 256, (24, 24), 114), (449, 256, (24, 24), 450), (449, 256, (48, 48), 449), (449, 128, (24, 24), 452)])
+def test_tar_tiles_share_the_cache_with_as_many_tables_as_fit(recorder, slices, D, grid, padded):  # noqa: F811
+    """The TaR tiles of a pass without old rows are numbered for whole groups of slices (1, 2, 4 or 8)."""
+    p = grid[0] * grid[1]
+    s = Stream(L=slices, H=1, D=D, grid=grid, cap=4 * p, budget=2 * p, r=1, entry=[0])
+    recorder.start()
+    assert s.call(4)[0] == ipv.OK
+    tar, = [x for x in recorder.launches() if x.kernel == "k_stretch_tar"]
+    tiles = -(-p // (256 * 16 // (2 * D)))  # a group of 256 threads: 256 / lanes a row columns of 4 frames
+    assert tar.grid_x == -(-padded * tiles // 8) * 8
+
+
 def compress_kernels(recorder, n, L, H, D, grid, r, dtype):  # noqa: F811
     """The kernels of one ipv_compress of n rows a slice."""
     s = ipv.Shape(1, L, H, D, n, *grid, dtype)
