@@ -3,7 +3,7 @@
 // A selection is one workgroup per slice, bound by its barriers: most of the
 // chip idles through it. What the next pass needs first does not depend on its
 // outcome: the value norms of the frames that come next, and the recent-key
-// table when the window lies in those frames. So these run in the selection's
+// table, if the window lies in those frames. So these run in the selection's
 // launch, on the CUs it leaves. 16x16 video (7 passes, 112 slices of 12288
 // rows): selection 26.6 us and the next table + VaN launch 41 us apart, 54 us
 // together (58 with one tile in flight, the same with four); 1114 -> 1056 us a call.
@@ -25,10 +25,10 @@ struct Ahead {
   int32_t kind;       // element type and head size: kind_of
   Stretch st;         // the next pass's
   int32_t n, r, p;
-  float* norm;        // patch_idx as floats, or null: no norms to compute
+  float* norm;        // patch_idx as floats
   FastDiv slices;
   uint32_t n_work, tile_blocks;
-  float* table;       // null: no table
+  float* table;       // null: no table (the consecutive-frame mode)
   FastDiv table_blocks;
   uint32_t table_real, table_padded;
   int32_t* first_recent;

@@ -288,7 +288,6 @@ __global__ void k_fill_i32(int32_t* p, int64_t count, int32_t v) {
 
 constexpr int kSelThreads = 1024;  // most threads of a selection workgroup
 constexpr int64_t kComputeUnits = 256;  // MI355X
-constexpr int64_t kAheadGroups = kComputeUnits * 3 / 4;
 
 // Threads of a selection workgroup: whole waves for the n rows at RPT rows a
 // thread, at most kSelThreads (the caller picks RPT >= n / kSelThreads).
@@ -415,24 +414,20 @@ ipv_status compact(const Dims& d, void* K, void* V, int32_t* fr, int32_t* pa, in
 // Scores of one pass over a run of slices. norms_known: van holds the old
 // rows' norms already. cv_tau: the TaR launch also computes the pooling CV.
 // zero_chunks > 0: the first kernel zeroes the flags of a gather that follows.
-// ahead: what the launch before has done already.
-struct AheadDone {
-  bool norms = false, table = false;
-};
-
+// ahead: this pass's first launch went out with the selection before it.
 template <typename T, int D>
 ipv_status stretch_scores_t(const Dims& d, const char* K, const char* V, const Stretch& sr, const int32_t* fr,
                             int32_t* pa, int32_t n, int32_t r, float* tar, float* van, void* ws, hipStream_t st,
-                            int64_t zero_chunks, bool adjacent, const double* cv_tau, bool norms_known, AheadDone ahead) {
+                            int64_t zero_chunks, bool adjacent, const double* cv_tau, bool norms_known, bool ahead) {
   using C = SweepCfg<T, D>;
   constexpr uint32_t TILE = C::GROUPS * C::U;
   uint32_t* zero = zero_chunks > 0 ? ws_flags(ws, d) : nullptr;
   const int32_t zero_per_slice = (int32_t)(compact_parts(d) * walk_words(zero_chunks));
   const uint32_t slices = (uint32_t)d.slices;
-  const uint32_t v0 = ahead.norms ? (uint32_t)n : norms_known ? sr.n0 : 0u;
+  const uint32_t v0 = ahead ? (uint32_t)n : norms_known ? sr.n0 : 0u;
   const uint32_t van_tiles = ((uint32_t)n - v0 + TILE - 1) / TILE, van_work = slices * van_tiles;
   const FastDiv van_div = make_fastdiv(std::max(1u, van_tiles));
-  int32_t* waiting = ahead.norms ? pa : nullptr;
+  int32_t* waiting = ahead ? pa : nullptr;
   int32_t* first = ws_first(ws, d);
   if (adjacent) {
     const uint32_t walks = pad8(slices), quads = pad8((van_work + 3) / 4);
@@ -445,10 +440,10 @@ ipv_status stretch_scores_t(const Dims& d, const char* K, const char* V, const S
     return launched();
   }
   const uint32_t blocks = (uint32_t)((d.p + C::GROUPS - 1) / C::GROUPS), table = slices * blocks;
-  if (!ahead.table)
+  if (!ahead)
     k_stretch_table_van<T, D><<<dim3(pad8(table) + pad8(van_work)), dim3(256), (size_t)C::GROUPS * r * sizeof(int32_t), st>>>(
-      K, V, sr, fr, pa, d.S, n, r, (int32_t)d.p, make_fastdiv(blocks), pad8(table), table, ws_table(ws), first,
-      err_word(ws), zero, zero_per_slice, van, v0, van_div, make_fastdiv(slices), van_work, pad8(van_work));
+        K, V, sr, fr, pa, d.S, n, r, (int32_t)d.p, make_fastdiv(blocks), pad8(table), table, ws_table(ws), first,
+        err_word(ws), zero, zero_per_slice, van, v0, van_div, make_fastdiv(slices), van_work, pad8(van_work));
   const uint32_t rows = sr.rows.d, new_frames = ((uint32_t)n - sr.n0) / rows;
   const uint32_t old_tiles = (sr.n0 + TILE - 1) / TILE, cols = (rows + C::GROUPS - 1) / C::GROUPS;
   const uint32_t tiles = old_tiles + (new_frames + C::U - 1) / C::U * cols;
@@ -465,7 +460,7 @@ ipv_status stretch_scores_t(const Dims& d, const char* K, const char* V, const S
 
 ipv_status stretch_scores(const Dims& d, const char* K, const char* V, const Stretch& sr, const int32_t* fr,
                           int32_t* pa, int32_t n, int32_t r, float* tar, float* van, void* ws, hipStream_t st,
-                          int64_t zero_chunks, bool adjacent, const double* cv_tau, bool norms_known, AheadDone ahead) {
+                          int64_t zero_chunks, bool adjacent, const double* cv_tau, bool norms_known, bool ahead) {
 #define IPV_SCORES(T, DD)                                                                                           \
   if (d.D == DD)                                                                                                    \
     return stretch_scores_t<T, DD>(d, K, V, sr, fr, pa, n, r, tar, van, ws, st, zero_chunks, adjacent, cv_tau, norms_known, \
@@ -480,21 +475,36 @@ ipv_status stretch_scores(const Dims& d, const char* K, const char* V, const Str
 }
 
 // ------------------------------------------------------------ work of the next pass (ipv_ahead.hpp)
-// Whether the next pass's first launch goes out with this pass's selection: while
-// that leaves a quarter of the CUs at least (a selection block fills one, so with
-// more blocks nothing would run beside it), and up to 16 rows a thread (longer
-// slices' selections use every register of a CU).
-bool ahead_fits(const Dims& d, int32_t n, uint32_t mode) {
+// Whether the next pass's first launch goes out with this pass's selection (n rows;
+// new_frames: the next pass's). A selection block fills a CU, so it pays while that
+// leaves CUs for the work beside it, the more the longer the rows. A call of five
+// passes without / with it, us, 196 rows a frame, bf16 rows of 256 bytes:
+//   28 slices of 2156 rows 138 / 119, of 12544 rows 362 / 333; 112 slices 223 / 220 and
+//   892 / 853; 128: 245 / 244 and 992 / 957; 144: 264 / 263 and 1092 / 1082; 160:
+//   281 / 288 and 1179 / 1169; 192: 319 / 329 and 1393 / 1402; head-shared, 80
+//   selections 902 / 894 and 4505 / 4451, 144: 433 / 442 and 2030 / 2033;
+//   rows of 128 bytes, 160 slices of 6272 rows 398 / 383; of 512 bytes, 112 slices
+//   835 / 818, 144 1035 / 1032 (of 1568 rows 344 / 342); of 1 KB, 64 slices 844 / 825,
+//   80 1031 / 1022 (of 2156 rows 418 / 422), 112 1410 / 1410, 144 1786 / 1805.
+// Up to 16 rows a thread: longer slices' selections use every register of a CU.
+// Only if the recent-key table goes with it (the window lies in the new frames):
+// the norms alone save no launch (28 slices of 1568 rows 123 / 128, 128 202 / 209).
+// The consecutive-frame mode has the norms beside its walks already, unless the
+// walks take most of the CUs and the selections do not: 56 head-shared selections
+// of 224 slices of 12544 rows 1808 / 1676, of 2156 rows 349 / 322, 28 of 112 slices
+// 1014 / 988 and 226 / 232, 4 of 16 426 / 441; 64 slices, each its own, 551 / 562.
+bool ahead_fits(const Dims& d, int32_t n, int32_t r, uint32_t mode, int32_t new_frames) {
   const int64_t groups = d.slices / ((mode & IPV_HEAD_SHARED) ? d.H : 1);
-  return groups <= kAheadGroups && n <= 16 * kSelThreads;
+  if (n > 16 * kSelThreads || groups > 192 - d.D * d.elem / 8) return false;
+  if (mode & IPV_TAR_ADJACENT) return 2 * groups <= d.slices && d.slices >= 96 && d.slices * n >= 300000;
+  return new_frames > r;
 }
 
 // The selection of a pass, with the first launch of the next one (next: its
 // rows, n_next of them; its new rows all lie in the frames).
 ipv_status select_ahead(const Dims& d, const float* tar, const float* van, int32_t* fr, int32_t* pa, int32_t n,
                         const Stretch& sr, int32_t budget, int32_t tar_total, int32_t r, const Emit& em, const char* K,
-                        const char* V, const Stretch& next, int32_t n_next, int64_t next_chunks, AheadDone what,
-                        void* ws, hipStream_t st, uint32_t mode) {
+                        const char* V, const Stretch& next, int32_t n_next, int64_t next_chunks, void* ws, hipStream_t st, uint32_t mode) {
   const uint32_t lpr = (uint32_t)(d.D * d.elem / 16), slices = (uint32_t)d.slices;
   const int32_t heads = (mode & IPV_HEAD_SHARED) ? (int32_t)d.H : 1;
   const uint32_t tile = 256u / lpr * 4u * kAheadTiles, tiles = ((uint32_t)n_next - next.n0 + tile - 1) / tile;
@@ -511,7 +521,7 @@ ipv_status select_ahead(const Dims& d, const float* tar, const float* van, int32
   a.slices = make_fastdiv(slices);
   a.n_work = slices * tiles;
   a.tile_blocks = pad8((a.n_work + 3) / 4);
-  if (what.table) {
+  if (!(mode & IPV_TAR_ADJACENT)) {
     a.table = ws_table(ws);
     a.table_blocks = make_fastdiv(blocks);
     a.table_real = slices * blocks;
@@ -1056,7 +1066,7 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
       ++passes[b];
     }
   };
-  AheadDone ahead;
+  bool ahead = false;  // the next pass's first launch is out
   for (;;) {
     // the next frame at which a stream reaches the cap (frames [pending, f] are its new rows)
     int64_t f = INT64_MAX;
@@ -1106,8 +1116,10 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
       if (!uniform && !small)
         IPV_TRY(stretch_scores(s, k, v, sr, fr, pa, n, r, tr, vn, ws, st, chunks, adjacent,
                                pool && !adjacent ? cv_tau : nullptr, l.pending > 0 && !pool, ahead));
-      ahead = AheadDone{};
       if (pool) IPV_TRY(pool_d(s, cv_tau, vn, fr, pa, n, sr, nullptr, ws, st, !adjacent));
+      // a group that is the whole batch stays alike, so the next pass is its own
+      ahead = s.B == d.B && !last && !uniform && !pool && !small && l.n0 <= budget &&
+              ahead_fits(s, n, r, mode, new_frames) && !small_pass(s, n_next, r, mode, cv_tau, kSmallFrameStretch);
       const Emit em{fr,
                     pa,
                     last ? places : keep,
@@ -1117,15 +1129,11 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
       if (small)
         IPV_TRY(run_small_stretch(s, k, v, sr, fr, pa, n, budget, floor_share(alpha, budget), r, mode, tr, vn,
                                   l.pending > 0 ? sr.n0 : 0u, em, last, ws, st));
-      else if (s.B == d.B && !last && !uniform && !pool && l.n0 <= budget && ahead_fits(s, n, mode) &&
-               !small_pass(s, n_next, r, mode, cv_tau, kSmallFrameStretch)) {  // the whole batch: it stays alike, so the next pass is its
-        const bool then_last = l.left == 2;
-        ahead.norms = true;
-        ahead.table = !adjacent && new_frames > r;
+      else if (ahead)
         IPV_TRY(select_ahead(s, tr, vn, fr, pa, n, sr, budget, floor_share(alpha, budget), r, em, k, v,
                              stretch(budget, (int32_t)f + 1, nullptr), n_next,
-                             then_last ? compact_chunks(budget) : 0, ahead, ws, st, mode));
-      } else
+                             l.left == 2 ? compact_chunks(budget) : 0, ws, st, mode));
+      else
         IPV_TRY(select(s, tr, vn, fr, n, sr, budget, floor_share(alpha, budget), r, keep, err_word(ws), st, mode,
                        uniform && last ? ws_flags(ws, s) : nullptr, (int32_t)(compact_parts(s) * walk_words(chunks)),
                        em));

@@ -35,18 +35,19 @@ CASES = {
     # more rows than 32 a selection thread, keep set over several stages
     "long": (1, 1, 32, (14, 14), 196, (0,), 180, 33000, 30000, 5, 33196, "bf16", 0, None),
     # the work of the next pass beside a selection: 4, 8, 12 and 16 rows a selection thread, odd capacities, windows as
-    # long as the new frames and longer (no table ahead), the largest number of selections it is done for and one more,
+    # long as the new frames and longer (nothing ahead), the largest number of selections it is done for and one more,
     # frames narrower than the grid, rows left in the cache above the budget (not in the first pass then)
     "ahead-4-rows": (2, 2, 128, (9, 13), 117, (0,), 60, 1700, 800, 3, 1819, "bf16", 0, None),
     "ahead-8-rows": (1, 3, 64, (14, 14), 196, (0,), 90, 5000, 2500, 4, 5199, "f32", 0, None),
     "ahead-12-rows": (1, 2, 32, (14, 14), 196, (0, 0), 120, 10000, 5000, 4, 10196, "bf16", ipv.TAR_REVERSE, None),
     "ahead-16-rows": (1, 2, 32, (14, 14), 196, (0,), 150, 15000, 8000, 4, 15197, "f32", ipv.HEAD_SHARED, None),
     "ahead-window-is-the-new-frames": (2, 2, 256, (5, 5), 25, (0,), 60, 500, 400, 4, 525, "bf16", 0, None),
-    "ahead-192-selections": (96, 2, 32, (6, 7), 42, (0,), 40, 600, 300, 2, 642, "bf16", 0, None),
-    "ahead-193-selections": (193, 1, 32, (6, 7), 42, (0,), 40, 600, 300, 2, 642, "bf16", 0, None),
+    "ahead-176-selections": (88, 2, 64, (6, 7), 42, (0,), 40, 600, 300, 2, 642, "bf16", 0, None),
+    "ahead-185-selections": (185, 1, 32, (6, 7), 42, (0,), 40, 600, 300, 2, 642, "bf16", 0, None),
     # TaR tiles of frames, 4 and 8 slices in turn, slices left over
     "4-slices-in-turn": (113, 2, 32, (5, 5), 25, (0,), 24, 300, 200, 2, 325, "bf16", 0, None),
     "8-slices-in-turn": (449, 1, 32, (5, 5), 25, (0,), 24, 300, 200, 2, 325, "bf16", 0, None),
+    "ahead-64-selections-of-1KB-rows": (32, 2, 256, (6, 7), 42, (0,), 20, 400, 200, 2, 442, "f32", 0, None),
     "ahead-narrow-frames": (1, 2, 64, (8, 8), 41, (20, 20), 60, 900, 400, 2, 943, "f32", ipv.VAN_REVERSE, None),
     "ahead-rows-above-the-budget": (1, 2, 128, (7, 7), 49, (900,), 80, 1000, 500, 2, 1049, "bf16", 0, None),
     # the first pass has 260 rows, the later ones 250 and go out as one launch each
@@ -59,6 +60,9 @@ CASES = {
     # one pass with few new rows in a call, then frames without one
     "in-cache": (2, 2, 128, (7, 7), 49, (1990, 1960, 1960), 6, 2000, 1600, 4, 2051, "bf16", ipv.HEAD_SHARED, None),
     "in-cache-pooled": (4, 1, 64, (7, 7), 30, (1990, 0, 1870), 8, 2000, 1600, 4, 2030, "f32", 0, (0.3, 0.5, 0.7)),
+    # the consecutive-frame mode: the norms only, where the walks take most of the CUs and the selections do not
+    "ahead-adjacent-half-the-slices": (224, 2, 32, (6, 7), 42, (0,), 40, 900, 400, 2, 943, "bf16",
+                                       ipv.TAR_ADJACENT | ipv.HEAD_SHARED, None),
     "ahead-adjacent": (2, 2, 256, (9, 13), 117, (0,), 60, 1700, 800, 3, 1819, "f32", ipv.TAR_ADJACENT, None),
     "ahead-adjacent-shared": (3, 2, 64, (9, 13), 117, (0, 0), 60, 1700, 1500, 4, 1817, "bf16",
                         ipv.TAR_ADJACENT | ipv.HEAD_SHARED, None),

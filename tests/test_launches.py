@@ -82,6 +82,28 @@ def test_tar_tiles_share_the_cache_with_as_many_tables_as_fit(recorder, slices, 
     assert tar.grid_x == -(-padded * tiles // 8) * 8
 
 
+@pytest.mark.parametrize("L,H,D,dtype,cap,budget,r,mode,ahead", [
+    (80, 8, 128, ipv.BF16, 6272, 3136, 4, ipv.HEAD_SHARED, True),
+    (28, 4, 128, ipv.BF16, 1568, 784, 4, 0, False), (28, 4, 128, ipv.BF16, 1568, 784, 3, 0, True),  # the window of all 4 new frames, of 3
+    (160, 1, 128, ipv.BF16, 6272, 3136, 4, 0, True), (161, 1, 128, ipv.BF16, 6272, 3136, 4, 0, False),
+    (64, 1, 256, ipv.F32, 6272, 3136, 4, 0, True), (65, 1, 256, ipv.F32, 6272, 3136, 4, 0, False),
+    (1, 4, 128, ipv.BF16, 16200, 8000, 4, 0, True), (1, 4, 128, ipv.BF16, 16600, 8000, 4, 0, False),
+    (28, 4, 128, ipv.BF16, 6272, 3136, 4, ipv.TAR_ADJACENT, False),
+    (28, 4, 128, ipv.BF16, 6272, 3136, 4, ipv.TAR_ADJACENT | ipv.HEAD_SHARED, True),
+    (28, 4, 128, ipv.BF16, 2352, 1176, 4, ipv.TAR_ADJACENT | ipv.HEAD_SHARED, False),
+    (4, 4, 128, ipv.BF16, 12544, 6272, 4, ipv.TAR_ADJACENT | ipv.HEAD_SHARED, False)])
+def test_the_next_passs_launch_goes_beside_few_selections(recorder, L, H, D, dtype, cap, budget, r, mode, ahead):  # noqa: F811
+    s = Stream(L=L, H=H, D=D, grid=(14, 14), cap=cap, budget=budget, r=r, entry=[0], dtype=dtype)
+    recorder.start()
+    rc, _, passes = s.call(-(-cap // 196) + 2 * -(-(cap - budget) // 196), mode)
+    assert rc == ipv.OK and passes == [3]
+    kernels = recorder.kernels()
+    assert kernels.count("k_select_ahead") == (2 if ahead else 0)
+    # without it each pass has a first launch of its own; with it only the first one, or the walks stay
+    walks = bool(mode & ipv.TAR_ADJACENT)
+    assert kernels.count("k_stretch_prev_van" if walks else "k_stretch_table_van") == (1 if ahead and not walks else 3)
+
+
 def compress_kernels(recorder, n, L, H, D, grid, r, dtype):  # noqa: F811
     """The kernels of one ipv_compress of n rows a slice."""
     s = ipv.Shape(1, L, H, D, n, *grid, dtype)
