@@ -75,8 +75,7 @@ __device__ __forceinline__ void ahead_block(const Ahead& a, const int32_t* frame
 // is a multiple of 8, so the rest map to XCDs as in a launch of their own.
 template <int RPT, bool VEC>
 __global__ __launch_bounds__(kAheadThreads) void k_select_ahead(const float* __restrict__ tar,
-                                                                const float* __restrict__ van,
-                                                                const int32_t* __restrict__ frame_idx,
+                                                                const float* van, const int32_t* frame_idx,
                                                                 const int32_t* patch_idx, int64_t S,
                                                                 int32_t n, int32_t budget, int32_t tar_total, int32_t r,
                                                                 uint32_t* err, int32_t heads, uint32_t tflip,

@@ -387,16 +387,30 @@ __device__ __forceinline__ void emit_rows(const Stretch& st, const Emit& em, int
   }
 }
 
+// What a selection reads. With a Stretch, emit_rows writes the metadata, the norms
+// and the keep set (which may be the old place index) where these point.
+template <class ST, class T>
+struct Input {
+  using Ptr = T* __restrict__;
+};
+template <class T>
+struct Input<Stretch, T> {
+  using Ptr = T*;
+};
+template <class ST, class T>
+using InputPtr = typename Input<ST, T>::Ptr;
+
 // One group of `heads` slices (1: a slice of its own) with NT threads. VEC:
 // every slice's row 0 is 16-byte aligned (capacity % 4 == 0) so row runs
 // load 16 bytes at a time. tflip / vflip: 0, or ~0 for a reversed stage.
 // With a Stretch, the keep set goes through emit_rows.
 template <int NT, int RPT, bool VEC, class ST, class EM>
-__device__ __forceinline__ void select_slice(const float* __restrict__ tar, const float* __restrict__ van,
-                             const int32_t* __restrict__ frame_idx, int64_t S, int32_t n, int32_t budget,
-                             int32_t tar_total, int32_t r, int32_t* __restrict__ keep_idx,
-                             uint32_t* err, int64_t slice, int32_t heads, uint32_t tflip, uint32_t vflip,
-                             SelShared<NT>& sh, const ST& st, const EM& em) {
+__device__ __forceinline__ void select_slice(const float* __restrict__ tar, InputPtr<ST, const float> van,
+                                             InputPtr<ST, const int32_t> frame_idx, int64_t S, int32_t n,
+                                             int32_t budget, int32_t tar_total, int32_t r,
+                                             InputPtr<ST, int32_t> keep_idx, uint32_t* err, int64_t slice,
+                                             int32_t heads, uint32_t tflip, uint32_t vflip, SelShared<NT>& sh,
+                                             const ST& st, const EM& em) {
   constexpr int NW = NT / kWave;
   const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
   const int64_t base = slice * S;
@@ -555,8 +569,8 @@ __device__ __forceinline__ bool uniform_taken(int64_t rank, int64_t k, int64_t q
 }
 
 template <int NT, int RPT, bool VEC, class ST, class EM>
-__device__ __forceinline__ void uniform_slice(const int32_t* __restrict__ frame_idx, int64_t S, int32_t n,
-                                              int32_t budget, int32_t r, int32_t* __restrict__ keep_idx,
+__device__ __forceinline__ void uniform_slice(InputPtr<ST, const int32_t> frame_idx, int64_t S, int32_t n,
+                                              int32_t budget, int32_t r, InputPtr<ST, int32_t> keep_idx,
                                               uint32_t* err, int64_t slice, int32_t heads, uint32_t* __restrict__ zero,
                                               int32_t zero_per_slice, SelShared<NT>& sh, const ST& st, const EM& em) {
   constexpr int NW = NT / kWave;
@@ -663,8 +677,8 @@ __device__ __forceinline__ void uniform_slice(const int32_t* __restrict__ frame_
 // head must hold the same frame ids and receives the same keep set).
 // zero (may be null): zero_per_slice words per slice to clear
 template <int NT, int RPT, bool VEC, class ST, class EM>
-__global__ __launch_bounds__(NT) void k_select_uniform(const int32_t* __restrict__ frame_idx, int64_t S, int32_t n,
-                                                       int32_t budget, int32_t r, int32_t* __restrict__ keep_idx,
+__global__ __launch_bounds__(NT) void k_select_uniform(InputPtr<ST, const int32_t> frame_idx, int64_t S, int32_t n,
+                                                       int32_t budget, int32_t r, InputPtr<ST, int32_t> keep_idx,
                                                        uint32_t* err, int32_t heads, uint32_t* __restrict__ zero,
                                                        int32_t zero_per_slice, ST st, EM em) {
   __shared__ SelShared<NT> sh;
@@ -676,10 +690,10 @@ __global__ __launch_bounds__(NT) void k_select_uniform(const int32_t* __restrict
 
 // grid: one block per group of `heads` consecutive slices
 template <int NT, int RPT, bool VEC, class ST, class EM>
-__global__ __launch_bounds__(NT) void k_select(const float* __restrict__ tar, const float* __restrict__ van,
-                                               const int32_t* __restrict__ frame_idx, int64_t S, int32_t n,
+__global__ __launch_bounds__(NT) void k_select(const float* __restrict__ tar, InputPtr<ST, const float> van,
+                                               InputPtr<ST, const int32_t> frame_idx, int64_t S, int32_t n,
                                                int32_t budget, int32_t tar_total, int32_t r,
-                                               int32_t* __restrict__ keep_idx, uint32_t* err, int32_t heads,
+                                               InputPtr<ST, int32_t> keep_idx, uint32_t* err, int32_t heads,
                                                uint32_t tflip, uint32_t vflip, ST st, EM em) {
   __shared__ SelShared<NT> sh;
   n = slice_rows(st, n, blockIdx.x * (uint32_t)heads);
