@@ -504,6 +504,7 @@ def main():
         "rows_per_s": round(B * L * H * w.n_tokens / (ms_per_step * 1e-3), 1),
         "algorithmic_bytes": algo,
         "step_us_mean": {k: round(v, 2) for k, v in step_us.items()},
+        "step_source": "events between launches of the steps (a pass of small slices is one launch in the timed loop)",
         "step_GBps": {k: round(v / (step_us[k] * 1e-6) / 1e9, 1) for k, v in algo_by_step.items()},
         "copy_ceiling_GBps": round(copy_gbps, 1),
         "roofline": {"bound": "hbm", "kernel": dom, "achieved": round(achieved, 1), "peak": PEAK_HBM_GBPS,

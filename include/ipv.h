@@ -228,15 +228,18 @@ ipv_status ipv_compress(const ipv_shape* shape, void* K, void* V, int32_t* frame
                         size_t ws_bytes, void* stream);
 
 /*
- * ipv_compress with per-kernel timing: each non-NULL entry of `at` is a
+ * ipv_compress with per-step timing: each non-NULL entry of `at` is a
  * hipEvent_t (created by the caller) recorded on `stream` at a step boundary:
  *   at[0] before the recent-key table   at[1] before the TaR/VaN sweep
  *   (IPV_TAR_ADJACENT: before the prev-row walk, before the adjacent sweep)
  *   at[2] before pooling                at[3] before selection
  *   at[4] before compaction             at[5] after compaction
- * Elapsed time between consecutive events is that step's device time. With
- * several runs of equal row counts the events are recorded in each run, so
- * they end up timing the last run.
+ * Elapsed time between consecutive events is that step's device time. A pass
+ * over slices so small that ipv_compress makes it in one launch takes a launch
+ * for each step here (the same results): its times are those of the steps, not
+ * of that launch. With events NULL the call is ipv_compress. Where the streams'
+ * row counts need several groups of launches the events are recorded in each
+ * group, so they end up timing the last one.
  */
 typedef struct {
   void* at[6];
