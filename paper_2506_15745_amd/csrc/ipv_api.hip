@@ -453,8 +453,8 @@ ipv_status stretch_scores_t(const Dims& d, const char* K, const char* V, const S
   const int32_t sure_past = (int32_t)std::max<int64_t>(0, (int64_t)n - (int64_t)r * d.p);
   k_stretch_tar<T, D><<<dim3(pad8(cv) + pad8(work)), dim3(256), 0, st>>>(
       K, sr, pa, waiting, d.S, n, (int32_t)d.p, ws_table(ws), first, tar, err_word(ws), make_fastdiv(tiles), old_tiles,
-      make_fastdiv(cols), work, pad8(work), slices, group, sure_past, van, (int32_t)d.H, cv ? cv_tau[0] : 0.0, cv ? cv_tau[1] : 0.0,
-      cv ? cv_tau[2] : 0.0, ws_pool(ws, d), pad8(cv), cv);
+      make_fastdiv(cols), work, pad8(work), slices, group, sure_past, van, (int32_t)d.H, cv ? cv_tau[0] : 0.0,
+      cv ? cv_tau[1] : 0.0, cv ? cv_tau[2] : 0.0, ws_pool(ws, d), pad8(cv), cv);
   return launched();
 }
 
@@ -504,7 +504,8 @@ bool ahead_fits(const Dims& d, int32_t n, int32_t r, uint32_t mode, int32_t new_
 // rows, n_next of them; its new rows all lie in the frames).
 ipv_status select_ahead(const Dims& d, const float* tar, const float* van, int32_t* fr, int32_t* pa, int32_t n,
                         const Stretch& sr, int32_t budget, int32_t tar_total, int32_t r, const Emit& em, const char* K,
-                        const char* V, const Stretch& next, int32_t n_next, int64_t next_chunks, void* ws, hipStream_t st, uint32_t mode) {
+                        const char* V, const Stretch& next, int32_t n_next, int64_t next_chunks, void* ws,
+                        hipStream_t st, uint32_t mode) {
   const uint32_t lpr = (uint32_t)(d.D * d.elem / 16), slices = (uint32_t)d.slices;
   const int32_t heads = (mode & IPV_HEAD_SHARED) ? (int32_t)d.H : 1;
   const uint32_t tile = 256u / lpr * 4u * kAheadTiles, tiles = ((uint32_t)n_next - next.n0 + tile - 1) / tile;
@@ -591,7 +592,7 @@ ipv_status stretch_gather(const Dims& d, void* K, void* V, const Stretch& sr, co
 // workgroup's share of the bandwidth counts: 512 rows of 256 bytes 17.8 -> 20.1,
 // of 64 bytes 16.5 -> 19.0, 512 slices of 64 bytes 42.8 -> 45.2. A caller that is
 // bound by its launches gains more (two passes and a gather of 128 rows: 7
-// launches -> 2, 38 -> 28 us a call).
+// launches -> 2, 38 -> 27 us a call).
 // The recent-key table takes the workgroup a round (with its own scan of the
 // window) for every 16 KB of key rows of one frame, and the tiles go over every
 // position of the grid, so the grid has to be small too. 256 rows of 256 bytes,

@@ -9,8 +9,9 @@
 // many is bandwidth, so the slice has to be small: see small_pass().
 //
 // Scores and the table go through global memory (the workgroup's own L1);
-// nothing here is `__restrict__`, so that the compiler does not take them for
-// constants and read them through the scalar cache.
+// no kernel argument is `__restrict__`, so that the compiler does not take them for
+// constants and read them through the scalar cache. (The steps' functions hold the
+// qualifier over their own extent, where it is true.)
 #pragma once
 
 #include "ipv_select.hpp"

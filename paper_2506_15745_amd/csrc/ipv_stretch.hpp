@@ -14,7 +14,7 @@
 // video of 192 frames (7 passes, 112 slices of 12288 rows) 2915 -> 1114 us a
 // call, a 64-frame 7B-class clip in calls of 16 frames 720 -> 557 us, a 172-frame
 // 72B-class clip (one pass) 8.41 -> 4.49 ms; with the later changes to the
-// selection, the tile order and the launches 1055 us, 556 us and 4.11 ms.
+// selection, the tile order and the launches 1046 us, 560 us and 4.12 ms.
 //
 // Row x of a slice is "old" (x < n0: it was a row of the slice before the
 // stretch's pending frames) or "new" (row x - n0 of the pending frames). An old
@@ -295,7 +295,8 @@ __device__ __forceinline__ void take_norm(int32_t* __restrict__ ahead, float* __
 template <typename T, int D>
 __device__ __forceinline__ void stretch_tar_new(const Stretch& st, int64_t S, uint32_t n, uint32_t p,
                                                 const float* __restrict__ table, uint32_t rec, float* __restrict__ tar,
-                                                int32_t* __restrict__ ahead, float* __restrict__ van, uint32_t slice, uint32_t f, uint32_t colblock, int tid) {
+                                                int32_t* __restrict__ ahead, float* __restrict__ van, uint32_t slice,
+                                                uint32_t f, uint32_t colblock, int tid) {
   using C = SweepCfg<T, D>;
   constexpr int EPL = C::EPL, LPR = C::LPR, GROUPS = C::GROUPS, U = C::U;
   constexpr uint32_t RB = D * (uint32_t)sizeof(T);
@@ -363,7 +364,8 @@ __global__ __launch_bounds__(256) void k_stretch_tar(const char* __restrict__ K,
                                                      const int32_t* __restrict__ first_recent, float* __restrict__ tar,
                                                      uint32_t* err, FastDiv tiles, uint32_t old_tiles, FastDiv col_blocks,
                                                      uint32_t n_work, uint32_t tile_blocks, uint32_t slices,
-                                                     uint32_t group, int32_t sure_past, float* van, int32_t H, double tau1, double tau2, double tau3,
+                                                     uint32_t group, int32_t sure_past, float* van, int32_t H,
+                                                     double tau1, double tau2, double tau3,
                                                      int32_t* __restrict__ pool_ws, uint32_t cv_padded,
                                                      uint32_t cv_real) {
   __shared__ double red[256 / kWave];

@@ -84,7 +84,8 @@ def test_tar_tiles_share_the_cache_with_as_many_tables_as_fit(recorder, slices, 
 
 @pytest.mark.parametrize("L,H,D,dtype,cap,budget,r,mode,ahead", [
     (80, 8, 128, ipv.BF16, 6272, 3136, 4, ipv.HEAD_SHARED, True),
-    (28, 4, 128, ipv.BF16, 1568, 784, 4, 0, False), (28, 4, 128, ipv.BF16, 1568, 784, 3, 0, True),  # the window of all 4 new frames, of 3
+    (28, 4, 128, ipv.BF16, 1568, 784, 4, 0, False),  # the window is all 4 new frames, 3 of them
+    (28, 4, 128, ipv.BF16, 1568, 784, 3, 0, True),
     (160, 1, 128, ipv.BF16, 6272, 3136, 4, 0, True), (161, 1, 128, ipv.BF16, 6272, 3136, 4, 0, False),
     (64, 1, 256, ipv.F32, 6272, 3136, 4, 0, True), (65, 1, 256, ipv.F32, 6272, 3136, 4, 0, False),
     (1, 4, 128, ipv.BF16, 16200, 8000, 4, 0, True), (1, 4, 128, ipv.BF16, 16600, 8000, 4, 0, False),
