@@ -1027,11 +1027,11 @@ ipv_status scratch_of(hipStream_t st, void** out) {
 // 175; 6: 178, 183; 12288 rows, 1 of 48: 311, 286; 4: 308, 300; 5: 307, 304; 6: 307,
 // 315, with pooling 351, 343; 80 slices of 32768 rows, 1 of 167: 586, 540; 12: 578,
 // 572; 16: 579, 586. The consecutive-frame mode and Uniform Select have no m vectors:
-// 165 and 165 (1 frame of 32), 94 and 94.
-bool pass_in_cache(int32_t n0, int32_t n, uint32_t mode, bool pool) {
-  if (mode & (IPV_TAR_ADJACENT | IPV_UNIFORM_SELECT)) return false;
-  return (int64_t)(n - n0) * (pool ? 8 : 10) <= n;
-}
+// 1 frame of 32 takes 165 and 166, 94 and 95 us; but in the cache the rows that stay
+// are compacted by more workgroups than select them: 48 slices of 50000 rows, half of
+// which stay, 1 new frame, 462 over the frames, 422 in the cache, with pooling 783,
+// 690, Uniform Select 239, 198.
+bool pass_in_cache(int32_t n0, int32_t n, bool pool) { return (int64_t)(n - n0) * (pool ? 8 : 10) <= n; }
 
 // Frames [0, n_frames) of a call of the continual-compression loop whose
 // arguments are checked: the passes run over the frames where they lie, one
@@ -1089,7 +1089,7 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
       float* tr = at_stream(tar, b0, rs);
       float* vn = at_stream(van, b0, rs);
       const bool small = small_pass(s, n, r, mode, cv_tau, kSmallFrameStretch);
-      if (last && l.pending == 0 && !small && pass_in_cache(l.n0, n, mode, pool)) {
+      if (last && l.pending == 0 && !small && pass_in_cache(l.n0, n, pool)) {
         IPV_TRY(append_run(d, b0, e, K, V, frame_idx, patch_idx, l.n0, fk, fv, rows, (int32_t)f + 1, frame_bytes,
                            first_frame_id, 0, st));
         IPV_TRY(compress_run(s, k, v, fr, pa, n, Whole{}, budget, alpha, r, mode, cv_tau, tr, vn, keep, ws, st, nullptr));

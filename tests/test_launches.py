@@ -27,7 +27,7 @@ def test_streams_alike_after_a_pass_share_its_launches(recorder, mode, tau, chai
 
 @pytest.mark.parametrize("frames,mode,tau,where", [
     (3, 0, None, "cache"), (4, 0, None, "frames"), (3, ipv.HEAD_SHARED, None, "cache"), (4, 0, (0.3, 0.5, 0.7), "cache"),
-    (5, 0, (0.3, 0.5, 0.7), "frames"), (1, ipv.TAR_ADJACENT, None, "frames"), (1, ipv.UNIFORM_SELECT, None, "frames")])
+    (5, 0, (0.3, 0.5, 0.7), "frames"), (1, ipv.TAR_ADJACENT, None, "cache"), (1, ipv.UNIFORM_SELECT, None, "cache")])
 def test_a_pass_with_few_new_rows_runs_in_the_cache(recorder, frames, mode, tau, where):  # noqa: F811
     s = Stream(L=28, H=4, D=128, grid=(14, 14), cap=6272, budget=3136, r=4, entry=[6272 - 196 * frames])
     recorder.start()
