@@ -317,7 +317,8 @@ ipv_status ipv_ckv_step(const ipv_shape* shape, void* K, void* V, int32_t* frame
  * its surviving rows are written into K and V once, after its last pass of the
  * call (the result is that of one append per frame and one compaction per
  * pass); the frames after that are appended. (A stream's only pass of a call,
- * if few of its rows are new, appends them and runs in the cache; a call whose
+ * if few of its rows are new, appends them and runs in the cache, as all passes do of
+ * a call on few slices with much metadata or with long slices to pool; a call whose
  * frames overlap K or V in memory goes through the loop frame by frame, each
  * frame read when its turn comes.)
  * Every step is checked before the first is enqueued (the counts of the

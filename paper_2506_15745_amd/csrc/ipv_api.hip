@@ -1033,10 +1033,37 @@ ipv_status scratch_of(hipStream_t st, void** out) {
 // 690, Uniform Select 239, 198.
 bool pass_in_cache(int32_t n0, int32_t n, bool pool) { return (int64_t)(n - n0) * (pool ? 8 : 10) <= n; }
 
+// Whether all passes of a call run in the cache, each after an append of its new
+// rows, because what they would do besides selecting costs more than they save.
+// n: most rows of a pass; passes: most of a stream; fresh: new rows of a pass; saved:
+// bytes that its appends and moves in the cache come to. A selection compacts the metadata of its slices by one
+// workgroup, a head after another, where the compaction in the cache has hundreds; the
+// pooling, a workgroup a slice, finds every row's frame through its place, three
+// times. Fitted to 13384 calls of 1 and 3 passes (1 to 8 selections, 1 to 8 heads, rows of
+// 64 to 512 bytes, 3136 to 60000 rows, budgets of 2/5 to 3/4), us a pass over the
+// frames against in the cache: +0.5 a thousand rows and head (1500 more a head: a
+// batch's latency), +20 for Uniform Select beyond 32768 rows (its registers spill
+// there), with pooling +2.5 a thousand rows beyond 8000 and +60 beyond 32768 rows,
+// -0.42 a saved MB, -6 for two launches less, +2 a call for the gather, and in the
+// consecutive-frame mode -2 a thousand fresh rows, which are not walked. Head-shared calls of 3 passes on one
+// layer, over the frames / in the cache / by this rule: 8 heads of 6272 rows of 128
+// bytes 205 / 170 / 170, 62000 rows 1893 / 1480 / 1480, 4 heads of 6272 rows 144 / 146
+// / 144; Uniform Select, 8 heads of 46000 rows 840 / 590 / 590; with pooling, 2
+// slices of 50000 rows 1833 / 1234 / 1234, 48 2578 / 2600 / 2570, 1 of 9000 243 / 239 /
+// 240.
+bool call_in_cache(const Dims& d, int32_t n, int32_t passes, int32_t budget, uint32_t mode, bool pool, int64_t fresh,
+                   int64_t saved) {
+  const double heads = (mode & IPV_HEAD_SHARED) ? (double)d.H : 1.0, spill = n > 32768 ? 1.0 : 0.0;
+  const double emit = 0.0005 * heads * (budget + 1500) + ((mode & IPV_UNIFORM_SELECT) ? 20.0 * spill : 0.0);
+  const double smooth = pool ? 0.0025 * std::max(n - 8000, 0) + 60.0 * spill : 0.0;
+  const double walk = (mode & IPV_TAR_ADJACENT) && scores_needed(mode) ? 0.002 * (double)fresh : 0.0;
+  return emit + smooth > 6.0 - 2.0 / passes + 0.42e-6 * (double)saved + walk;
+}
+
 // Frames [0, n_frames) of a call of the continual-compression loop whose
 // arguments are checked: the passes run over the frames where they lie, one
 // gather per stream follows its last pass, and the frames after that are
-// appended (a stream's only pass may run in the cache: pass_in_cache). The places
+// appended (or in the cache: call_in_cache, pass_in_cache). The places
 // of a stream's rows between two passes are kept in its rows of keep_idx, its
 // value norms in van (without pooling, which overwrites them); the last pass
 // leaves its keep set and scores there, and the places of the rows that stay in
@@ -1052,6 +1079,10 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
   const bool pool = cv_tau && !uniform;
   auto fires_in = [&](int32_t n) { return (mem_cap - n + rows - 1) / rows; };  // frames until the cap, the last included
   std::vector<LoopStream> ls((size_t)d.B);
+  int64_t fresh = 0, moved = 0;  // rows of a slice that the streams' passes bring; that those in the cache move
+  int64_t fired = 0, firsts = 0, laters = 0;  // streams that fire; groups of them in first passes (alike in their
+                                              // rows) and in later ones (in the frame of the first pass)
+  int32_t most = 1, n_most = 0;   // most passes of a stream and rows of a pass
   for (int64_t b = 0; b < d.B; ++b) {
     ls[b] = {n_tokens[b], 0, 0};
     // a budget equal to the cap fires once: the checks let no frame follow that pass
@@ -1060,7 +1091,18 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
       ++ls[b].left;
       if (later < 1) break;
     }
+    if (ls[b].left == 0) continue;
+    ++fired;
+    const bool begins = b == 0 || ls[b - 1].left == 0;
+    firsts += begins || n_tokens[b] != n_tokens[b - 1];
+    laters += begins || fires_in(n_tokens[b]) != fires_in(n_tokens[b - 1]);
+    fresh += (fires_in(n_tokens[b]) + (ls[b].left - 1) * later) * rows;
+    moved += (int64_t)(ls[b].left - 1) * budget;
+    most = std::max(most, ls[b].left);
+    n_most = std::max<int32_t>(n_most, n_tokens[b] + fires_in(n_tokens[b]) * rows);
   }
+  const bool in_cache = fired && call_in_cache(d, n_most, most, budget, mode, pool, fresh / (fired * most),
+                                               2 * d.L * d.H * (fresh + moved) * d.D * d.elem / (firsts + laters * (most - 1)));
   auto done = [&](int64_t b, int64_t e, int64_t f) {  // streams [b, e) had a pass at frame f
     for (; b < e; ++b) {
       ls[b] = {budget, (int32_t)f + 1, ls[b].left - 1};
@@ -1089,9 +1131,10 @@ ipv_status stream_part(const Dims& d, void* K, void* V, int32_t* frame_idx, int3
       float* tr = at_stream(tar, b0, rs);
       float* vn = at_stream(van, b0, rs);
       const bool small = small_pass(s, n, r, mode, cv_tau, kSmallFrameStretch);
-      if (last && l.pending == 0 && !small && pass_in_cache(l.n0, n, pool)) {
-        IPV_TRY(append_run(d, b0, e, K, V, frame_idx, patch_idx, l.n0, fk, fv, rows, (int32_t)f + 1, frame_bytes,
-                           first_frame_id, 0, st));
+      if (in_cache || (last && l.pending == 0 && !small && pass_in_cache(l.n0, n, pool))) {
+        IPV_TRY(append_run(d, b0, e, K, V, frame_idx, patch_idx, l.n0, fk + l.pending * frame_bytes,
+                           fv + l.pending * frame_bytes, rows, (int32_t)f + 1 - l.pending, frame_bytes,
+                           first_frame_id + l.pending, 0, st));
         IPV_TRY(compress_run(s, k, v, fr, pa, n, Whole{}, budget, alpha, r, mode, cv_tau, tr, vn, keep, ws, st, nullptr));
         done(b0, e, f);
         return IPV_OK;

@@ -63,6 +63,14 @@ CASES = {
     # the consecutive-frame mode: the norms only, where the walks take most of the CUs and the selections do not
     "ahead-adjacent-half-the-slices": (224, 2, 32, (6, 7), 42, (0,), 40, 900, 400, 2, 943, "bf16",
                                        ipv.TAR_ADJACENT | ipv.HEAD_SHARED, None),
+    # all passes of a call in the cache: much metadata on one workgroup
+    "call-in-cache": (1, 8, 32, (14, 14), 196, (0, 500), 60, 5000, 3800, 4, 5199, "bf16", ipv.HEAD_SHARED, None),
+    "call-in-cache-uniform": (1, 4, 32, (14, 14), 150, (2900,), 70, 8000, 6000, 3, 8150, "f32",
+                              ipv.HEAD_SHARED | ipv.UNIFORM_SELECT, None),
+    "call-in-cache-pooled": (1, 8, 32, (7, 7), 49, (0, 0, 4900), 120, 5000, 4000, 4, 5049, "bf16",
+                             ipv.HEAD_SHARED | ipv.VAN_REVERSE, (0.3, 0.5, 0.7)),
+    "call-in-cache-long-pooled": (1, 2, 32, (14, 14), 196, (0, 20000), 240, 26000, 13000, 4, 26195, "bf16", 0,
+                                  (0.3, 0.5, 0.7)),
     "ahead-adjacent": (2, 2, 256, (9, 13), 117, (0,), 60, 1700, 800, 3, 1819, "f32", ipv.TAR_ADJACENT, None),
     "ahead-adjacent-shared": (3, 2, 64, (9, 13), 117, (0, 0), 60, 1700, 1500, 4, 1817, "bf16",
                         ipv.TAR_ADJACENT | ipv.HEAD_SHARED, None),

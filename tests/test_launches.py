@@ -38,6 +38,47 @@ def test_a_pass_with_few_new_rows_runs_in_the_cache(recorder, frames, mode, tau,
     assert ("k_stretch_gather" in kernels) == (where == "frames")
 
 
+@pytest.mark.parametrize("L,H,D,cap,mode,in_cache", [
+    (1, 8, 64, 6272, ipv.HEAD_SHARED, True), (1, 2, 64, 6272, ipv.HEAD_SHARED, False), (28, 4, 128, 6272, ipv.HEAD_SHARED, False),
+    (1, 8, 256, 6272, ipv.HEAD_SHARED, False), (1, 4, 64, 31000, ipv.HEAD_SHARED | ipv.UNIFORM_SELECT, True),
+    (1, 1, 64, 46000, ipv.UNIFORM_SELECT, True), (1, 1, 64, 12000, ipv.UNIFORM_SELECT, False), (1, 1, 64, 12000, 0, False),
+    (1, 8, 64, 20000, ipv.HEAD_SHARED | ipv.TAR_ADJACENT, True), (1, 4, 64, 20000, ipv.HEAD_SHARED | ipv.TAR_ADJACENT, False)])
+def test_a_call_with_much_metadata_on_few_workgroups_runs_in_the_cache(recorder, L, H, D, cap, mode, in_cache):  # noqa: F811
+    budget = cap * 3 // 4
+    s = Stream(L=L, H=H, D=D, grid=(14, 14), cap=cap, budget=budget, r=4, entry=[0])
+    first, later = -(-cap // 196), -(-(cap - budget) // 196)
+    recorder.start()
+    rc, n, passes = s.call(first + 2 * later + 1, mode)
+    assert rc == ipv.OK and passes == [3] and n == [budget + 196]
+    kernels = recorder.kernels()
+    assert kernels.count("k_append") == (4 if in_cache else 1) and kernels.count("k_compact") == (3 if in_cache else 0)
+    assert any("stretch" in k for k in kernels) != in_cache
+
+
+@pytest.mark.parametrize("L,H,D,cap,mode,in_cache", [
+    (1, 2, 64, 50000, 0, True), (1, 1, 64, 26000, 0, True), (1, 1, 64, 9000, 0, False), (6, 8, 64, 50000, 0, False),
+    (2, 1, 64, 50000, ipv.TAR_ADJACENT, True), (1, 1, 64, 16000, ipv.TAR_ADJACENT, False), (28, 4, 128, 6272, 0, False)])
+def test_a_call_with_pooling_over_few_long_slices_runs_in_the_cache(recorder, L, H, D, cap, mode, in_cache):  # noqa: F811
+    budget = cap // 2
+    s = Stream(L=L, H=H, D=D, grid=(14, 14), cap=cap, budget=budget, r=4, entry=[0])
+    recorder.start()
+    rc, n, passes = s.call(-(-cap // 196) + 2 * -(-(cap - budget) // 196), mode, (0.3, 0.5, 0.7))
+    assert rc == ipv.OK and passes == [3] and n == [budget]
+    kernels = recorder.kernels()
+    assert kernels.count("k_append") == (3 if in_cache else 0) and any("stretch" in k for k in kernels) != in_cache
+
+
+@pytest.mark.parametrize("apart", [196, 1, 0])
+def test_streams_that_are_compressed_apart_count_apart(recorder, apart):  # noqa: F811
+    """What the passes over the frames save is set against the selections of as many launches as the streams take
+    (streams of different counts take launches of their own also in a pass at the same frame)."""
+    s = Stream(L=1, H=8, D=64, grid=(14, 14), cap=6272, budget=4704, r=4, entry=[apart * b for b in range(8)])
+    recorder.start()
+    rc, n, passes = s.call(32, ipv.HEAD_SHARED)
+    assert rc == ipv.OK and passes == [1] * 8
+    assert any("stretch" in k for k in recorder.kernels()) == (apart == 0)
+
+
 @pytest.mark.parametrize("frames_at,cache,apart", [
     ("fK", "K", False), ("fV", "V", False), ("fK", "V", False), ("fV", "K", False), ("fK", "K", True), ("fV", "V", True)])
 def test_frames_in_the_caches_memory_go_frame_by_frame(recorder, frames_at, cache, apart):  # noqa: F811
