@@ -1036,21 +1036,22 @@ bool pass_in_cache(int32_t n0, int32_t n, bool pool) { return (int64_t)(n - n0) 
 // Whether all passes of a call run in the cache, each after an append of its new
 // rows, because what they would do besides selecting costs more than they save.
 // n: most rows of a pass; passes: most of a stream; fresh: new rows of a pass; saved:
-// bytes that its appends and moves in the cache come to. A selection compacts the metadata of its slices by one
-// workgroup, a head after another, where the compaction in the cache has hundreds; the
-// pooling, a workgroup a slice, finds every row's frame through its place, three
-// times. Fitted to 13384 calls of 1 and 3 passes (1 to 8 selections, 1 to 8 heads, rows of
-// 64 to 512 bytes, 3136 to 60000 rows, budgets of 2/5 to 3/4), us a pass over the
-// frames against in the cache: +0.5 a thousand rows and head (1500 more a head: a
-// batch's latency), +20 for Uniform Select beyond 32768 rows (its registers spill
-// there), with pooling +2.5 a thousand rows beyond 8000 and +60 beyond 32768 rows,
-// -0.42 a saved MB, -6 for two launches less, +2 a call for the gather, and in the
-// consecutive-frame mode -2 a thousand fresh rows, which are not walked. Head-shared calls of 3 passes on one
-// layer, over the frames / in the cache / by this rule: 8 heads of 6272 rows of 128
-// bytes 205 / 170 / 170, 62000 rows 1893 / 1480 / 1480, 4 heads of 6272 rows 144 / 146
-// / 144; Uniform Select, 8 heads of 46000 rows 840 / 590 / 590; with pooling, 2
-// slices of 50000 rows 1833 / 1234 / 1234, 48 2578 / 2600 / 2570, 1 of 9000 243 / 239 /
-// 240.
+// bytes that its appends and moves in the cache come to. A selection compacts the
+// metadata of its slices by one workgroup, a head after another, where the compaction
+// in the cache has hundreds; the pooling, a workgroup a slice, finds every row's frame
+// through its place, three times. Fitted to 13384 calls of 1 and 3 passes (1 to 8
+// selections, 1 to 8 heads, rows of 64 to 512 bytes, 3136 to 60000 rows, budgets of
+// 2/5 to 3/4), us a pass over the frames against in the cache: +0.5 a thousand rows
+// and head (1500 more a head: a batch's latency), +20 for Uniform Select beyond 32768
+// rows (its registers spill there), with pooling +2.5 a thousand rows beyond 8000 and
+// +60 beyond 32768 rows, -0.42 a saved MB, -6 for two launches less, +2 a call for the
+// gather, and in the consecutive-frame mode -2 a thousand fresh rows, which are not
+// walked. Calls of 3 passes, rows of 128 bytes, over the frames / in the cache:
+// head-shared on one layer, budget 3/4, 8 heads of 6272 rows 201 / 157, of 60000 1996
+// / 1355, 4 heads of 3136 109 / 110, of 6272 139 / 130, 2 of 6272 (not by this rule)
+// 113 / 121; Uniform Select, 8 heads of 46000 rows 840 / 571; with pooling, budget
+// 1/2, 2 slices of 50000 rows 1833 / 1234, 48 (not by this rule) 2574 / 2599, 1 of
+// 9000 (not by this rule) 244 / 242.
 bool call_in_cache(const Dims& d, int32_t n, int32_t passes, int32_t budget, uint32_t mode, bool pool, int64_t fresh,
                    int64_t saved) {
   const double heads = (mode & IPV_HEAD_SHARED) ? (double)d.H : 1.0, spill = n > 32768 ? 1.0 : 0.0;
